@@ -1,0 +1,105 @@
+"""The predictor's products at the shapes where a kernel or the choice between
+kernels can go wrong: batches around the 16-row tiles, widths around the tiles
+and the stages of K, and one shape past each line of the dispatch."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2605_20150_amd import predictor as P
+
+pytestmark = pytest.mark.gpu
+
+
+def say(msg):
+    print(msg, flush=True)
+
+
+def reference(mlp, x, y, ok):
+    """Logits, loss and gradients in double precision with the weights the
+    products read (bfloat16) and the FP32 biases, and the hidden units (of the
+    one hidden layer) whose sign is certain on every row: their pre-activation
+    is further from zero than the products' error bound 2^-14 sum |w a|.  A
+    unit nearer than that may be cut by the ReLU on one side only."""
+    Ws = [w.to(torch.bfloat16).double() for w, _ in mlp.split(mlp.params)]
+    bs = [b.double() for _, b in mlp.split(mlp.params)]
+    acts = [x.double()]
+    for l, (w, b) in enumerate(zip(Ws, bs)):
+        z = acts[-1] @ w.T + b
+        acts.append(z if l + 1 == len(Ws) else torch.relu(z))
+    z = acts[-1]
+    count = x.shape[0] * ok.sum()
+    loss = ((torch.clamp(z, min=0) - z * y + torch.log1p(torch.exp(-z.abs()))) * ok).sum() / count
+    G = (torch.sigmoid(z) - y) * ok / count
+    grads = [None] * len(Ws)
+    for l in range(len(Ws) - 1, -1, -1):
+        grads[l] = (G.T @ acts[l], G.sum(0))
+        if l:
+            G = (G @ Ws[l]) * (acts[l] > 0)
+    S = acts[0].abs() @ Ws[0].abs().T + bs[0].abs()
+    sure = ((acts[0] @ Ws[0].T + bs[0]).abs() > 2.0 ** -14 * S).all(0)
+    return z, loss, grads, sure
+
+
+# dims, batch: what they reach
+CASES = [
+    ([8, 8, 32], 1),               # one chunk of K, one row, tiles mostly past the edge
+    ([24, 40, 96], 16),            # K cut inside a chunk; a full 16-row tile
+    ([112, 264, 288], 17),         # two row tiles in the direct kernel; K past one 256-deep stage by a chunk
+    ([16, 72, 16384], 33),         # direct kernel, 64-row tiles; 64 stages
+    ([16, 520, 544], 64),          # input gradient with a cut last stage and a cut column tile
+    ([16, 72, 8192], 65),          # 64 x 64 tiles forward, ragged rows
+    ([16, 136, 65536], 129),       # 128 x 128 tiles forward and in the weight gradient, ragged both ways
+    ([16, 16392, 64], 130),        # 128 x 128 tiles in the input gradient, ragged columns
+]
+
+
+@pytest.mark.parametrize("dims,batch", CASES)
+def test_products_match_double_precision(dims, batch):
+    say(f"case: dims {dims} batch {batch}")
+    mlp = P.MLP(dims, seed=91)
+    g = torch.Generator(device="cuda").manual_seed(92)
+    mlp.params.add_(0.05 * torch.randn(mlp.P, generator=g, device="cuda"))
+    mlp.set_weights([w.cpu().numpy() for w, _ in mlp.split(mlp.params)], [b.cpu().numpy() for _, b in mlp.split(mlp.params)])
+    x = torch.randn((batch, dims[0]), generator=g, device="cuda")
+    n = dims[-1]
+    lab = torch.randint(0, 1 << 31, (batch, n // 32), generator=g, device="cuda", dtype=torch.int64).to(torch.int32)
+    valid = torch.full((n // 32,), -1, dtype=torch.int32, device="cuda")
+    valid[-1] = 0x00FFFFFF
+    shift = torch.arange(32, device="cuda", dtype=torch.int32)
+    y = ((lab[..., None] >> shift) & 1).reshape(batch, -1).double()
+    ok = ((valid[:, None] >> shift) & 1).reshape(1, -1).double()
+    z = mlp.forward(x)
+    loss = mlp.backward(x, z, lab, valid)
+    ref_z, ref_loss, ref_g, sure = reference(mlp, x, y, ok)
+    # an FP32 operand enters as two bf16 halves (relative error 2^-17 at most),
+    # a layer's sums and the next layers' weights pass it on: 2^-14 of the
+    # output's norm covers the two layers with an FP32 sum's own rounding
+    rel = float((z.double() - ref_z).norm() / ref_z.norm())
+    say(f"logits {rel:.2e} loss {float(loss) - float(ref_loss):.2e}")
+    assert rel <= 2.0 ** -14
+    assert abs(float(loss) - float(ref_loss)) <= 2.0 ** -14 * abs(float(ref_loss))
+    # the weight gradient drops the lo x lo term of its two split operands
+    # (2^-18 of a product) besides; a first-layer row is judged where its unit's
+    # sign is certain
+    say(f"{int((~sure).sum())} of {sure.numel()} units near zero")
+    assert (~sure).float().mean() <= 0.05 or sure.numel() < 100
+    for l, ((gw, gb), (rw, rb)) in enumerate(zip(mlp.split(mlp.grad), ref_g)):
+        for name, a, b in (("W", gw, rw), ("b", gb, rb)):
+            if l == 0:
+                a, b = a[sure], b[sure]
+            rel = float((a.double() - b).norm() / b.norm())
+            say(f"layer {l} d{name} {rel:.2e}")
+            assert rel <= 1e-4
+
+
+def test_every_kernel_gives_a_row_the_same_bits():
+    """The forward kernels share one accumulation order, so a row's logits do
+    not depend on the batch it comes in."""
+    dims = [112, 512, 65536]
+    mlp = P.MLP(dims, seed=93)
+    g = torch.Generator(device="cuda").manual_seed(94)
+    x = torch.randn((200, dims[0]), generator=g, device="cuda")
+    full = mlp.forward(x).clone()
+    for b in (1, 16, 17, 32, 33, 64, 65, 128):
+        say(f"case: batch {b} of 200")
+        assert torch.equal(mlp.forward(x[:b]), full[:b])
