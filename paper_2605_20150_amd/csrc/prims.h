@@ -62,6 +62,30 @@ struct OffsetsOut {   // out[i] = off
   bool aligned() const { return ((uintptr_t)out & 15) == 0; }
 };
 
+// out[i] = off, and mark[b] = i for every multiple of 2^kMarkShift that falls in
+// [off, off + v): where a walk over equal pieces of the flattened lists starts.
+// mark[0, n_mark) only.
+constexpr int kMarkShift = 6;
+struct OffsetsMarkOut {
+  uint32_t* out;
+  uint32_t* mark;
+  uint32_t n_mark;
+  __device__ void marks(int64_t i, uint32_t off, uint32_t v) const {
+    const uint64_t end = (uint64_t)off + v;
+    for (uint64_t b = ((uint64_t)off + ((1u << kMarkShift) - 1)) >> kMarkShift; (b << kMarkShift) < end && b < n_mark; ++b)
+      mark[b] = (uint32_t)i;
+  }
+  __device__ void operator()(int64_t i, uint32_t off, uint32_t v) const {
+    out[i] = off;
+    marks(i, off, v);
+  }
+  __device__ void store4(int64_t i, const uint32_t* off, const uint32_t* v) const {
+    *reinterpret_cast<uint4*>(out + i) = make_uint4(off[0], off[1], off[2], off[3]);
+    for (int k = 0; k < 4; ++k) marks(i + k, off[k], v[k]);
+  }
+  bool aligned() const { return ((uintptr_t)out & 15) == 0; }
+};
+
 // Extras written by whichever block holds the total: a u32 copy of it,
 // end[n] = total (the closing offset of an offsets array), and a copy of
 // copy_n u64 words from copy_src (read after the total is stored, so it may
@@ -232,6 +256,24 @@ inline void scan_exclusive(In in, int64_t n, uint32_t* out, unsigned long long* 
 }
 
 inline size_t scan_partial_count(int64_t n) { return (size_t)ceil_div(n > 0 ? n : 1, kScanTile); }
+
+// The entry that element e of a flattened list of lists falls in: the largest
+// s in [0, n) with off[s] <= e (off ascending, off[0] <= e), for a whole wave
+// with the same arguments.  64 candidates a round, so five rounds reach 2^30
+// entries; ends and stays in bounds whatever off holds.
+__device__ inline uint32_t pair_of(const uint32_t* __restrict__ off, uint32_t n, uint32_t e) {
+  const uint32_t lane = __lane_id();
+  uint32_t lo = 0, hi = n;   // off[lo] <= e, and off[hi] > e where hi < n
+  while (hi - lo > 1) {
+    const uint32_t step = (hi - lo + kWave - 1) / kWave;
+    const uint32_t d = lane * step;
+    const bool in = d < hi - lo && (lane == 0 || off[lo + d] <= e);
+    const uint32_t top = 63 - __builtin_clzll(__ballot(in));   // lane 0 always counts
+    lo += top * step;
+    hi = hi - lo > step ? lo + step : hi;
+  }
+  return lo;
+}
 
 // ------------------------------------------------------------- radix sort
 inline size_t radix_hist_count(int64_t n) { return 256 * (size_t)ceil_div(n > 0 ? n : 1, kSortTile); }

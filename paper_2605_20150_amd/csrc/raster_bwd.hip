@@ -30,8 +30,13 @@ struct __attribute__((aligned(sizeof(T)))) Rec9 {
 // 32 entries is done, lane k adds entry k's four row sums, applies the
 // entry's factors (opacity, conic) and stores its partial.  (Batches of 32 keep the parked sums at the LDS size that 64
 // entries with rows added in pairs took, so occupancy is unchanged, and each
-// taken entry saves the nine pair additions.)  Entries no pixel reaches get
-// zero partials.
+// taken entry saves the nine pair additions.)  An entry some pixel takes is
+// marked in `taken` (one byte per emission index, zero on entry unless mark_all,
+// which has the kernel write every byte); the others get no partial, and the
+// per-pair sums pass over them.  At street level most entries lie behind the
+// last contributor of every pixel: their zero records of 36 bytes, scattered by
+// emission index, were most of the kernel's time (20M Gaussians, 4 x 1600x900:
+// 9580 us with them, 635 us without).
 template <typename T>
 __global__ void __launch_bounds__(64) k_render_bwd(const uint32_t* __restrict__ order,
                                                    const uint32_t* __restrict__ ranges,
@@ -40,7 +45,8 @@ __global__ void __launch_bounds__(64) k_render_bwd(const uint32_t* __restrict__ 
                                                    int32_t Tx, int32_t Ty, int32_t W, int32_t H, T bg0, T bg1,
                                                    T bg2, const T* __restrict__ tfin,
                                                    const uint32_t* __restrict__ last_in,
-                                                   const T* __restrict__ dimg, T* __restrict__ partial) {
+                                                   const T* __restrict__ dimg, T* __restrict__ partial,
+                                                   uint8_t* __restrict__ taken, int mark_all) {
   const int nt = Tx * Ty;
   const int g = (int)order[blockIdx.x];
   const int c = g / nt, t = g - c * nt;
@@ -86,12 +92,10 @@ __global__ void __launch_bounds__(64) k_render_bwd(const uint32_t* __restrict__ 
     const uint32_t o = __shfl_xor(maxl, off, kWave);
     maxl = o > maxl ? o : maxl;
   }
-  const uint32_t start = ranges[2 * g], end = ranges[2 * g + 1];
-  for (uint32_t j = start + maxl + lane; j < end; j += 64) {
-    Rec9<T> z;
-#pragma unroll
-    for (int m = 0; m < kG2; ++m) z.v[m] = 0;
-    *reinterpret_cast<Rec9<T>*>(partial + (int64_t)inst_e[j] * kG2) = z;
+  const uint32_t start = ranges[2 * g];
+  if (mark_all) {
+    const uint32_t end = ranges[2 * g + 1];
+    for (uint32_t j = start + maxl + lane; j < end; j += 64) taken[inst_e[j]] = 0;
   }
   __shared__ T s_u[64], s_v[64], s_Ah[64], s_Bh[64], s_Ch[64], s_A[64], s_B[64], s_C[64], s_o[64], s_r[64],
       s_g[64], s_b[64];
@@ -214,26 +218,24 @@ __global__ void __launch_bounds__(64) k_render_bwd(const uint32_t* __restrict__ 
       }
     }
     __syncthreads();
-    if (lane < n) {
+    if (lane < n && ((hit >> lane) & 1u)) {
       Rec9<T> r;
-      if ((hit >> lane) & 1u) {
 #pragma unroll
-        for (int m = 0; m < kG2; ++m)
-          r.v[m] = (s_part[lane][0][m] + s_part[lane][1][m]) + (s_part[lane][2][m] + s_part[lane][3][m]);
-        // dpower/du = A dx + B dy, dpower/dv = B dx + C dy, dpower/dA =
-        // -dx^2/2, dpower/dB = -dx dy, dpower/dC = -dy^2/2; dL/dpower =
-        // opacity t
-        const T op = s_o[lane], p1 = r.v[0], s1 = r.v[1];
-        r.v[0] = op * (s_A[lane] * p1 + s_B[lane] * s1);
-        r.v[1] = op * (s_B[lane] * p1 + s_C[lane] * s1);
-        r.v[2] *= (T)-0.5 * op;
-        r.v[3] *= -op;
-        r.v[4] *= (T)-0.5 * op;
-      } else {
-#pragma unroll
-        for (int m = 0; m < kG2; ++m) r.v[m] = 0;
-      }
+      for (int m = 0; m < kG2; ++m)
+        r.v[m] = (s_part[lane][0][m] + s_part[lane][1][m]) + (s_part[lane][2][m] + s_part[lane][3][m]);
+      // dpower/du = A dx + B dy, dpower/dv = B dx + C dy, dpower/dA =
+      // -dx^2/2, dpower/dB = -dx dy, dpower/dC = -dy^2/2; dL/dpower =
+      // opacity t
+      const T op = s_o[lane], p1 = r.v[0], s1 = r.v[1];
+      r.v[0] = op * (s_A[lane] * p1 + s_B[lane] * s1);
+      r.v[1] = op * (s_B[lane] * p1 + s_C[lane] * s1);
+      r.v[2] *= (T)-0.5 * op;
+      r.v[3] *= -op;
+      r.v[4] *= (T)-0.5 * op;
       *reinterpret_cast<Rec9<T>*>(partial + (int64_t)my_e * kG2) = r;
+      taken[my_e] = 1;
+    } else if (mark_all && lane < n) {
+      taken[my_e] = 0;
     }
     uint32_t r2 = 0;
     if (v2) r2 = inst_rec[e2];
@@ -271,66 +273,203 @@ __device__ __forceinline__ void seg_step(int p, T (&v)[kG2]) {
   }
 }
 
-// Per visible pair, the sum of its instances' partials; one wave64 workgroup
-// per 64 consecutive depth-ordered visible pairs.  Their partials are
-// contiguous ([inst_off[s0], inst_off[s0 + 64])), so the wave
-// walks them 64 instances at a time with coalesced loads; each lane finds its
-// pair by binary search over the 64 offsets, a segmented inclusive scan in
-// DPP (row shifts 1, 2, 4, 8, then the broadcasts of lanes 15 and 31; no LDS
-// round trips) sums equal-pair lanes, and the last lane of each segment adds
-// into that pair's LDS accumulator.  A pair gets at most one add per step and
-// steps run in order, so the sums are deterministic.  Balanced whatever the
-// footprint sizes.
-template <typename T>
+// Per visible pair, the sum of its instances' partials, in an order fixed by
+// the lists alone: the pairs go in groups of 64 (depth order), a group's
+// contiguous instances in steps of 64 from its first; a step sums equal-pair
+// lanes by a segmented inclusive scan in DPP (row shifts 1, 2, 4, 8, then the
+// broadcasts of lanes 15 and 31; no LDS round trips), and a pair adds up its
+// steps' sums one after the other.
+//
+// One wave64 workgroup takes the steps that start in its `piece` of the
+// instances: it finds its first pair by a 64-way search of inst_off, a lane its
+// pair by binary search over the group's 64 offsets in LDS.  Split by steps,
+// not by groups: the nearest pairs come first and cover thousands of tiles each
+// at street level, and the wave that took 64 of them ran long after the rest
+// (20M Gaussians, 4 x 1600x900: 8220 us by groups, 310 us now; 1M from above,
+// where footprints are even: 174 and 170 us).
+// A pair that goes on past the piece is finished here (kWhole), or its sum so
+// far is left in the piece's tail and the later pieces leave its steps' sums in
+// `head`, which k_reduce_spans adds on in order: one launch more, but no wave
+// waits for a pair of thousands of tiles.  A pair covers at most a view's
+// tiles, so the first form is taken up to kWholeTiles tiles a view (16 steps
+// past the piece).
+//
+// Instances that are not `taken` have no partial (their record is not read),
+// and 64 of them in a row cost one load; a pair without a taken one gets no sum
+// (its gradients are zero), and the others are marked in g2d_on (one byte per
+// record, zero on entry unless mark_all, which writes every visible pair's).
+constexpr int64_t kReduceMin = kWave, kReduceMax = 2048;
+constexpr int64_t kWholeTiles = 1024;
+inline int64_t reduce_piece(int64_t n_inst) {
+  const int64_t p = ceil_div(ceil_div(n_inst, 8192), kWave) * kWave;   // 8192 waves fill the chip
+  return p < kReduceMin ? kReduceMin : (p > kReduceMax ? kReduceMax : p);
+}
+
+template <typename T, bool kWhole>
 __global__ void __launch_bounds__(64) k_reduce_pairs(const uint32_t* __restrict__ vis_rec,
-                                                     const uint32_t* __restrict__ inst_off, int64_t n_vis,
-                                                     int64_t n_rec, const T* __restrict__ partial,
-                                                     T* __restrict__ g2d) {
+                                                     const uint32_t* __restrict__ inst_off, uint32_t n_vis,
+                                                     uint32_t n_inst, uint32_t piece, const T* __restrict__ partial,
+                                                     const uint8_t* __restrict__ taken, T* __restrict__ g2d,
+                                                     uint8_t* __restrict__ g2d_on, int mark_all,
+                                                     T* __restrict__ head, T* __restrict__ tail,
+                                                     int64_t* __restrict__ tail_pair) {
   const int lane = threadIdx.x;
-  const int64_t s0 = (int64_t)blockIdx.x * kWave;
-  const int np = (int)(n_vis - s0 < kWave ? n_vis - s0 : kWave);
+  const int64_t c = blockIdx.x;
+  const uint32_t b0 = (uint32_t)c * piece;
+  const uint32_t b1 = n_inst - b0 > piece ? b0 + piece : n_inst;
   __shared__ uint32_t s_off[kWave + 1];
   __shared__ T s_acc[kWave][kG2];
-  if (lane <= np) s_off[lane] = inst_off[s0 + lane];
-  if (lane == 0 && np == kWave) s_off[kWave] = inst_off[s0 + kWave];
-#pragma unroll
-  for (int m = 0; m < kG2; ++m) s_acc[lane][m] = 0;
-  __syncthreads();
-  const uint32_t e0 = s_off[0], e1 = s_off[np];
-  for (uint32_t base = e0; base < e1; base += kWave) {
-    const uint32_t e = base + (uint32_t)lane;
-    const bool valid = e < e1;
-    int lo = 0, hi = np;   // s_off[lo] <= e < s_off[hi]
-    while (hi - lo > 1) {
-      const int mid = (lo + hi) >> 1;
-      if (s_off[mid] <= e) lo = mid;
-      else hi = mid;
-    }
-    const int p = valid ? lo : -1;
-    // one record load (a lane's 36 bytes as two 16-byte loads and one
-    // 4-byte load: nine single loads at a 36-byte stride made every load
-    // instruction touch 36 cache segments)
-    const Rec9<T> rec = *reinterpret_cast<const Rec9<T>*>(partial + (int64_t)(valid ? e : e0) * kG2);
-    T v[kG2];
-#pragma unroll
-    for (int m = 0; m < kG2; ++m) v[m] = valid ? rec.v[m] : (T)0;
-    seg_step<0x111, 0xF>(p, v);   // row_shr:1
-    seg_step<0x112, 0xF>(p, v);   // row_shr:2
-    seg_step<0x114, 0xF>(p, v);   // row_shr:4
-    seg_step<0x118, 0xF>(p, v);   // row_shr:8
-    seg_step<0x142, 0xA>(p, v);   // row_bcast:15 into rows 1 and 3
-    seg_step<0x143, 0xC>(p, v);   // row_bcast:31 into rows 2 and 3
-    const bool seg_end = valid && (lane == kWave - 1 || e + 1 == s_off[lo + 1]);
-    if (seg_end) {
-#pragma unroll
-      for (int m = 0; m < kG2; ++m) s_acc[p][m] += v[m];
-    }
+  __shared__ uint8_t s_on[kWave];   // pairs with a taken instance
+  int64_t open = -1;                // the pair that goes on past this piece
+  for (uint32_t s0 = pair_of(inst_off, n_vis, b0) & ~63u; s0 < n_vis; s0 += kWave) {
+    const int np = (int)(n_vis - s0 < (uint32_t)kWave ? n_vis - s0 : (uint32_t)kWave);
     __syncthreads();
-  }
-  if (lane < np) {
-    const uint32_t r = vis_rec[s0 + lane];
+    if (lane <= np) s_off[lane] = inst_off[s0 + lane];
+    if (lane == 0 && np == kWave) s_off[kWave] = inst_off[s0 + kWave];
 #pragma unroll
-    for (int m = 0; m < kG2; ++m) g2d[(int64_t)r * kG2 + m] = s_acc[lane][m];
+    for (int m = 0; m < kG2; ++m) s_acc[lane][m] = 0;
+    s_on[lane] = 0;
+    __syncthreads();
+    const uint32_t g0 = s_off[0], g1 = s_off[np];
+    if (g0 >= b1) break;
+    // first step of the group that starts in this piece, and the end of its steps
+    const uint32_t x0 = g0 >= b0 ? g0 : g0 + (b0 - g0 + kWave - 1) / kWave * kWave;
+    if (x0 >= g1) continue;
+    const uint32_t x1 = g1 < b1 ? g1 : b1;                // steps start below x1
+    const uint32_t ns = (x1 - x0 - 1) / kWave + 1;        // x0 < x1: a piece holds a step's length or more
+    const uint64_t xe = (uint64_t)x0 + (uint64_t)ns * kWave;   // where the next piece's steps go on
+    // the pair begun in an earlier piece (the one across x0), or none
+    int hp = -1;
+    if (x0 > g0) {
+      const uint64_t before = __ballot(lane < np && s_off[lane] < x0);   // the group's first pair at least
+      const int q = 63 - __builtin_clzll(before);
+      if (s_off[q + 1] > x0) hp = q;
+    }
+    // a step's sums, into the accumulators (only: of that pair alone, or of all if negative)
+    // the mark of a step's lane, loaded a step ahead
+    auto mark = [&](uint32_t xs) -> uint8_t { return xs < g1 && g1 - xs > (uint32_t)lane ? taken[xs + lane] : 0; };
+    uint8_t tk = mark(x0);
+    auto step = [&](uint32_t xs, int only) {
+      const uint32_t x = xs + lane;
+      const bool valid = g1 - xs > (uint32_t)lane;
+      const bool on = tk != 0;
+      tk = mark(xs + kWave);
+      const bool heads = !kWhole && hp >= 0 && s_off[hp + 1] > xs;   // hp's part goes to head
+      T* hd = head + (int64_t)(xs / kWave) * kG2;
+      if (__ballot(on) == 0) {
+        if (heads && lane < kG2) hd[lane] = 0;
+        return;
+      }
+      int lo = 0, hi = np;   // s_off[lo] <= x < s_off[hi]
+      while (hi - lo > 1) {
+        const int mid = (lo + hi) >> 1;
+        if (s_off[mid] <= x) lo = mid;
+        else hi = mid;
+      }
+      const int p = valid ? lo : -1;
+      T v[kG2];
+#pragma unroll
+      for (int m = 0; m < kG2; ++m) v[m] = 0;
+      if (on) {
+        // one record load (a lane's 36 bytes as two 16-byte loads and one
+        // 4-byte load: nine single loads at a 36-byte stride made every load
+        // instruction touch 36 cache segments)
+        const Rec9<T> rec = *reinterpret_cast<const Rec9<T>*>(partial + (int64_t)x * kG2);
+#pragma unroll
+        for (int m = 0; m < kG2; ++m) v[m] = rec.v[m];
+        s_on[lo] = 1;
+      }
+      seg_step<0x111, 0xF>(p, v);   // row_shr:1
+      seg_step<0x112, 0xF>(p, v);   // row_shr:2
+      seg_step<0x114, 0xF>(p, v);   // row_shr:4
+      seg_step<0x118, 0xF>(p, v);   // row_shr:8
+      seg_step<0x142, 0xA>(p, v);   // row_bcast:15 into rows 1 and 3
+      seg_step<0x143, 0xC>(p, v);   // row_bcast:31 into rows 2 and 3
+      const bool seg_end = valid && (lane == kWave - 1 || x + 1 == s_off[lo + 1]);
+      if (seg_end && (only < 0 || p == only)) {
+        if (heads && p == hp) {
+#pragma unroll
+          for (int m = 0; m < kG2; ++m) hd[m] = v[m];
+        } else {
+#pragma unroll
+          for (int m = 0; m < kG2; ++m) s_acc[p][m] += v[m];
+        }
+      }
+      __syncthreads();
+    };
+    for (uint32_t k = 0; k < ns; ++k) step(x0 + k * kWave, -1);
+    const bool mine = lane < np && s_off[lane] >= x0 && s_off[lane] < xe;
+    const bool opens = mine && xe < g1 && s_off[lane + 1] > xe;
+    const uint64_t om = __ballot(opens);   // one pair at most: the one across xe
+    if (kWhole && om) {
+      const int q = __builtin_ctzll(om);
+      const uint32_t y0 = (uint32_t)xe, more = (s_off[q + 1] - y0 - 1) / kWave + 1;
+      for (uint32_t k = 0; k < more; ++k) step(y0 + k * kWave, q);
+    }
+    if (mine) {
+      T* dst = nullptr;
+      if (!kWhole && opens) {
+        dst = tail + c * kG2;
+      } else if (s_on[lane] || mark_all) {
+        const int64_t r = vis_rec[s0 + lane];
+        g2d_on[r] = s_on[lane];
+        if (s_on[lane]) dst = g2d + r * kG2;
+      }
+      if (dst) {
+#pragma unroll
+        for (int m = 0; m < kG2; ++m) dst[m] = s_acc[lane][m];
+      }
+    }
+    if (!kWhole && om) open = (int64_t)s0 + __builtin_ctzll(om);
+    if (g1 >= b1) break;
+  }
+  if (!kWhole && lane == 0) tail_pair[c] = open;
+}
+
+// The pairs that span pieces: the tail of the piece a pair begins in plus the
+// sums of its later steps, in order.  Nine threads a piece, one per value; eight
+// steps' loads in flight.
+template <typename T>
+__global__ void __launch_bounds__(256) k_reduce_spans(const uint32_t* __restrict__ vis_rec,
+                                                      const uint32_t* __restrict__ inst_off, int64_t pieces,
+                                                      uint32_t piece, const T* __restrict__ head,
+                                                      const T* __restrict__ tail,
+                                                      const int64_t* __restrict__ tail_pair, T* __restrict__ g2d,
+                                                      uint8_t* __restrict__ g2d_on) {
+  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  const int64_t c = i / kG2;
+  const int m = (int)(i - c * kG2);
+  if (c >= pieces) return;
+  const int64_t p = tail_pair[c];
+  if (p < 0) return;
+  const int64_t g0 = inst_off[p & ~63ll], end = inst_off[p + 1];
+  const int64_t b1 = (c + 1) * (int64_t)piece;
+  const int64_t x0 = g0 + (b1 - g0 + kWave - 1) / kWave * kWave;   // first step past the piece
+  const int64_t n = (end - x0 + kWave - 1) / kWave;
+  T v = tail[c * kG2 + m];
+  int64_t k = 0;
+  for (; k + 8 <= n; k += 8) {
+    T h[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) h[u] = head[((x0 >> 6) + k + u) * kG2 + m];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) v += h[u];
+  }
+  for (; k < n; ++k) v += head[((x0 >> 6) + k) * kG2 + m];
+  const int64_t r = vis_rec[p];
+  g2d[r * kG2 + m] = v;
+  if (m == 0) g2d_on[r] = 1;
+}
+
+// Zeroes n bytes (a kernel: the call may be captured), 16 per thread.
+__global__ void __launch_bounds__(256) k_clear(uint8_t* __restrict__ p, int64_t n) {
+  const int64_t stride = 16 * (int64_t)gridDim.x * 256;
+  for (int64_t i = 16 * ((int64_t)blockIdx.x * 256 + threadIdx.x); i < n; i += stride) {
+    if (i + 16 <= n && ((uintptr_t)p & 15) == 0) {
+      *reinterpret_cast<uint4*>(p + i) = make_uint4(0u, 0u, 0u, 0u);
+    } else {
+      for (int64_t j = i; j < n && j < i + 16; ++j) p[j] = 0;
+    }
   }
 }
 
@@ -464,8 +603,9 @@ __device__ __forceinline__ void adj_colour_cam(const ShK<T>& K, const DevCam<T>&
   }
 }
 
-// Thread per processing index; only active rows work.  Each kept camera's
-// 36-byte record of 2-D gradients is read once, as one object: pass 1 chains
+// Thread per processing index; only active rows work.  The 36-byte record of
+// 2-D gradients of each camera in which some pixel took the row (g2d_on;
+// the others add nothing) is read once, as one object: pass 1 chains
 // its geometry part (u, v, conic) back to mean, log-scale and quaternion,
 // cameras in order, and parks its opacity and colour part in LDS; pass 2
 // runs the opacity and then the colour, one channel at a time (that
@@ -491,7 +631,7 @@ struct AdamRows {
 
 template <typename T, bool kAdam>
 __device__ __forceinline__ void adjoint_row(T* params, const int32_t* __restrict__ order, int32_t B, int64_t n_pidx,
-                                            const CamSet<T>& cs, const uint32_t* __restrict__ tt,
+                                            const CamSet<T>& cs, const uint32_t* __restrict__ tt, const uint8_t* __restrict__ g2d_on,
                                             const uint32_t* __restrict__ active, const uint32_t* __restrict__ act_idx,
                                             const T* __restrict__ g2d, T* __restrict__ grad, int64_t ld,
                                             const AdamRows<T>& ad) {
@@ -504,7 +644,7 @@ __device__ __forceinline__ void adjoint_row(T* params, const int32_t* __restrict
   const int V = cs.n;
   uint32_t keepm = 0;
 #pragma unroll 1
-  for (int c = 0; c < V; ++c) keepm |= (tt[(int64_t)c * n_pidx + i] != 0 ? 1u : 0u) << c;
+  for (int c = 0; c < V; ++c) keepm |= ((!tt || tt[(int64_t)c * n_pidx + i] != 0) && g2d_on[(int64_t)c * n_pidx + i] != 0 ? 1u : 0u) << c;
   T bcx = 0, bcy = 0;
   if constexpr (kAdam) adam_step_bias<T>(ad.step + (int64_t)slot * B + row, ad.lb1, ad.lb2, bcx, bcy);
   // Adam state (m, v) of column j; a group of columns loads its states
@@ -640,11 +780,11 @@ __device__ __forceinline__ void adjoint_row(T* params, const int32_t* __restrict
 
 template <typename T>
 __global__ void __launch_bounds__(256) k_adjoint(T* params, const int32_t* __restrict__ order, int32_t B,
-                                                 int64_t n_pidx, CamSet<T> cs, const uint32_t* __restrict__ tt,
+                                                 int64_t n_pidx, CamSet<T> cs, const uint32_t* __restrict__ tt, const uint8_t* __restrict__ g2d_on,
                                                  const uint32_t* __restrict__ active,
                                                  const uint32_t* __restrict__ act_idx, const T* __restrict__ g2d,
                                                  T* __restrict__ grad, int64_t ld) {
-  adjoint_row<T, false>(params, order, B, n_pidx, cs, tt, active, act_idx, g2d, grad, ld, AdamRows<T>{});
+  adjoint_row<T, false>(params, order, B, n_pidx, cs, tt, g2d_on, active, act_idx, g2d, grad, ld, AdamRows<T>{});
 }
 
 // The fused variant holds the Adam state of the row besides the adjoint's:
@@ -652,23 +792,25 @@ __global__ void __launch_bounds__(256) k_adjoint(T* params, const int32_t* __res
 template <typename T>
 __global__ void __launch_bounds__(256, 4) k_adjoint_adam(T* params, const int32_t* __restrict__ order, int32_t B,
                                                          int64_t n_pidx, CamSet<T> cs,
-                                                         const uint32_t* __restrict__ tt,
+                                                         const uint32_t* __restrict__ tt, const uint8_t* __restrict__ g2d_on,
                                                          const uint32_t* __restrict__ active,
                                                          const uint32_t* __restrict__ act_idx,
                                                          const T* __restrict__ g2d, AdamRows<T> ad) {
-  adjoint_row<T, true>(params, order, B, n_pidx, cs, tt, active, act_idx, g2d, nullptr, 0, ad);
+  adjoint_row<T, true>(params, order, B, n_pidx, cs, tt, g2d_on, active, act_idx, g2d, nullptr, 0, ad);
 }
 
 template <typename T>
-static void launch_adjoint(const tide_pool* pool, const tide_proj* proj, const CamSet<T>& cs, const T* g2d,
+static void launch_adjoint(const tide_pool* pool, const tide_proj* proj, const CamSet<T>& cs, const uint32_t* tt,
+                           const uint8_t* g2d_on, const T* g2d,
                            T* grad, int64_t ld, hipStream_t st) {
   hipLaunchKernelGGL(k_adjoint<T>, dim3((uint32_t)ceil_div(proj->n_pidx, 256)), dim3(256), 0, st,
-                     (T*)pool->params, pool->order, pool->block_rows, proj->n_pidx, cs, proj->tiles_touched,
+                     (T*)pool->params, pool->order, pool->block_rows, proj->n_pidx, cs, tt, g2d_on,
                      proj->active, proj->act_idx, g2d, grad, ld);
 }
 
 template <typename T>
-static void launch_adjoint_adam(const tide_pool* pool, const tide_proj* proj, const CamSet<T>& cs, const T* g2d,
+static void launch_adjoint_adam(const tide_pool* pool, const tide_proj* proj, const CamSet<T>& cs, const uint32_t* tt,
+                           const uint8_t* g2d_on, const T* g2d,
                                 const tide_adam_cfg* cfg, hipStream_t st) {
   AdamRows<T> ad;
   ad.m1 = (T*)pool->exp_avg;
@@ -678,7 +820,7 @@ static void launch_adjoint_adam(const tide_pool* pool, const tide_proj* proj, co
   ad.lb1 = std::log2((double)cfg->beta1);
   ad.lb2 = std::log2((double)cfg->beta2);
   hipLaunchKernelGGL(k_adjoint_adam<T>, dim3((uint32_t)ceil_div(proj->n_pidx, 256)), dim3(256), 0, st,
-                     (T*)pool->params, pool->order, pool->block_rows, proj->n_pidx, cs, proj->tiles_touched,
+                     (T*)pool->params, pool->order, pool->block_rows, proj->n_pidx, cs, tt, g2d_on,
                      proj->active, proj->act_idx, g2d, ad);
 }
 
@@ -689,67 +831,101 @@ CamSet<T> make_camset(const tide_camera* cams, int n);
 
 using namespace tide;
 
+// Up to here every mark is written by the kernels (131072 scattered bytes cost
+// less than the 5 us of a clearing launch).
+constexpr int64_t kMarkAllMax = 1 << 17;
+
+namespace {
+// The backward's workspace: per instance the partial and its taken mark, per
+// pair the sum, per step and piece of the pair sums what spans pieces.
+template <typename T>
+struct BwdWs {
+  T *partial, *g2d, *head, *tail;
+  uint8_t *taken, *g2d_on;   // adjacent: cleared together
+  int64_t n_clear;
+  int64_t* tail_pair;
+  int64_t piece, pieces;
+  size_t bytes;
+  BwdWs(void* base, const tide_bins* bins) {
+    const int64_t n = bins->n_inst > 0 ? bins->n_inst : 1;
+    piece = reduce_piece(n);
+    pieces = ceil_div(n, piece);
+    Carver cv(base);
+    partial = cv.take<T>((size_t)n * kG2);
+    g2d = cv.take<T>((size_t)kG2 * bins->n_cams * bins->n_pidx);
+    head = cv.take<T>((size_t)kG2 * ceil_div(n, kWave));
+    tail = cv.take<T>((size_t)kG2 * pieces);
+    tail_pair = cv.take<int64_t>(pieces);
+    const int64_t nr = (int64_t)bins->n_cams * bins->n_pidx;
+    taken = cv.take<uint8_t>(n);
+    g2d_on = cv.take<uint8_t>(nr);
+    n_clear = (int64_t)align_up(n) + nr;
+    bytes = cv.used + 256;
+  }
+};
+}  // namespace
+
 extern "C" size_t tide_render_bwd_ws_bytes(const tide_bins* bins, int32_t dtype) {
   if (!bins) return 0;
-  const size_t es = dtype == TIDE_F64 ? 8 : 4;
-  return align_up((size_t)(bins->n_inst > 0 ? bins->n_inst : 1) * kG2 * es) +
-         align_up((size_t)kG2 * bins->n_cams * bins->n_pidx * es) + 256;
+  return dtype == TIDE_F64 ? BwdWs<double>(nullptr, bins).bytes : BwdWs<float>(nullptr, bins).bytes;
 }
 
-// The three stages on one stream; with cfg the last one applies the masked
+// The stages on one stream; with cfg the last one applies the masked
 // Adam update instead of storing the gradient.
+template <typename T>
+static tide_status render_bwd_t(const tide_pool* pool, const tide_camera* cams, int32_t n_cams, const tide_proj* proj,
+                                const tide_bins* bins, const tide_frame* fr, const float* bg, const void* d_dimage,
+                                void* grad, int64_t grad_ld, const tide_adam_cfg* cfg, void* ws, hipStream_t st) {
+  const uint32_t grid = (uint32_t)(bins->n_cams * bins->tiles_x * bins->tiles_y);
+  const BwdWs<T> w(ws, bins);
+  const int64_t ni = bins->n_inst;
+  // Few instances: the kernels write every mark themselves, a launch saved (and
+  // the adjoint looks at the tile counts to tell the pairs that have one); many:
+  // the marks are cleared up front and only the taken ones written (scattered).
+  const int mark_all = ni <= kMarkAllMax ? 1 : 0;
+  const uint32_t* tt = mark_all ? proj->tiles_touched : nullptr;
+  if (!mark_all) {
+    const int64_t nb = ceil_div(w.n_clear, 16 * 256);
+    hipLaunchKernelGGL(k_clear, dim3((uint32_t)(nb < 4096 ? nb : 4096)), dim3(256), 0, st, w.taken, w.n_clear);
+    TIDE_LAUNCH_CHECK("k_clear");
+  }
+  TIDE_TIMED("render_bwd", st, hipLaunchKernelGGL(k_render_bwd<T>, dim3(grid), dim3(64), 0, st, bins->tile_order, bins->ranges, bins->inst_e, bins->inst_rec,
+                     (const T*)proj->rec, bins->tiles_x, bins->tiles_y, fr->width, fr->height, (T)bg[0], (T)bg[1],
+                     (T)bg[2], (const T*)fr->t_final, fr->last, (const T*)d_dimage, w.partial, w.taken, mark_all));
+  TIDE_LAUNCH_CHECK("k_render_bwd");
+  if (bins->n_vis > 0 && ni > 0) {
+    const bool whole = (int64_t)bins->tiles_x * bins->tiles_y <= kWholeTiles || w.pieces == 1;
+    auto reduce = whole ? k_reduce_pairs<T, true> : k_reduce_pairs<T, false>;
+    TIDE_TIMED("reduce_pairs", st, hipLaunchKernelGGL(reduce, dim3((uint32_t)w.pieces), dim3(kWave), 0, st,
+                                                      bins->vis_rec, bins->inst_off, (uint32_t)bins->n_vis,
+                                                      (uint32_t)ni, (uint32_t)w.piece, w.partial, w.taken, w.g2d,
+                                                      w.g2d_on, mark_all, w.head, w.tail, w.tail_pair));
+    TIDE_LAUNCH_CHECK("k_reduce_pairs");
+    if (!whole) {
+      hipLaunchKernelGGL(k_reduce_spans<T>, dim3((uint32_t)ceil_div(kG2 * w.pieces, 256)), dim3(256), 0, st,
+                         bins->vis_rec, bins->inst_off, w.pieces, (uint32_t)w.piece, w.head, w.tail, w.tail_pair, w.g2d,
+                         w.g2d_on);
+      TIDE_LAUNCH_CHECK("k_reduce_spans");
+    }
+  }
+  const CamSet<T> cs = make_camset<T>(cams, n_cams);
+  if (proj->n_pidx > 0) {
+    if (cfg)
+      TIDE_TIMED("adjoint_adam", st, launch_adjoint_adam<T>(pool, proj, cs, tt, w.g2d_on, w.g2d, cfg, st));
+    else
+      TIDE_TIMED("adjoint", st, launch_adjoint<T>(pool, proj, cs, tt, w.g2d_on, w.g2d, (T*)grad, grad_ld, st));
+  }
+  TIDE_LAUNCH_CHECK("k_adjoint");
+  return TIDE_OK;
+}
+
 static tide_status render_bwd_run(const tide_pool* pool, const tide_camera* cams, int32_t n_cams,
                                   const tide_proj* proj, const tide_bins* bins, const tide_frame* fr, const float* bg,
                                   const void* d_dimage, void* grad, int64_t grad_ld, const tide_adam_cfg* cfg,
                                   void* ws, hipStream_t st) {
-  const uint32_t grid = (uint32_t)(bins->n_cams * bins->tiles_x * bins->tiles_y);
-  const int64_t nrec = (int64_t)n_cams * proj->n_pidx;
-  Carver cv(ws);
-  if (proj->dtype == TIDE_F32) {
-    float* partial = cv.take<float>((size_t)(bins->n_inst > 0 ? bins->n_inst : 1) * kG2);
-    float* g2d = cv.take<float>((size_t)kG2 * nrec);
-
-    TIDE_TIMED("render_bwd", st, hipLaunchKernelGGL(k_render_bwd<float>, dim3(grid), dim3(64), 0, st, bins->tile_order, bins->ranges, bins->inst_e, bins->inst_rec,
-                       (const float*)proj->rec, bins->tiles_x, bins->tiles_y, fr->width, fr->height, bg[0], bg[1],
-                       bg[2], (const float*)fr->t_final, fr->last, (const float*)d_dimage, partial));
-    TIDE_LAUNCH_CHECK("k_render_bwd");
-    if (bins->n_vis > 0)
-      TIDE_TIMED("reduce_pairs", st, hipLaunchKernelGGL(k_reduce_pairs<float>, dim3((uint32_t)ceil_div(bins->n_vis, kWave)),
-                                                        dim3(kWave), 0, st, bins->vis_rec, bins->inst_off, bins->n_vis, nrec,
-                                                        (const float*)partial, g2d));
-    TIDE_LAUNCH_CHECK("k_reduce_pairs");
-    const CamSet<float> cs = make_camset<float>(cams, n_cams);
-    if (proj->n_pidx > 0) {
-      if (cfg)
-        TIDE_TIMED("adjoint_adam", st, launch_adjoint_adam<float>(pool, proj, cs, g2d, cfg, st));
-      else
-        TIDE_TIMED("adjoint", st, launch_adjoint<float>(pool, proj, cs, g2d, (float*)grad, grad_ld, st));
-    }
-    TIDE_LAUNCH_CHECK("k_adjoint");
-  } else {
-    double* partial = cv.take<double>((size_t)(bins->n_inst > 0 ? bins->n_inst : 1) * kG2);
-    double* g2d = cv.take<double>((size_t)kG2 * nrec);
-
-    TIDE_TIMED("render_bwd", st, hipLaunchKernelGGL(k_render_bwd<double>, dim3(grid), dim3(64), 0, st, bins->tile_order, bins->ranges, bins->inst_e,
-                       bins->inst_rec, (const double*)proj->rec, bins->tiles_x, bins->tiles_y, fr->width,
-                       fr->height, (double)bg[0], (double)bg[1], (double)bg[2], (const double*)fr->t_final,
-                       fr->last, (const double*)d_dimage, partial));
-    TIDE_LAUNCH_CHECK("k_render_bwd");
-    if (bins->n_vis > 0)
-      TIDE_TIMED("reduce_pairs", st, hipLaunchKernelGGL(k_reduce_pairs<double>, dim3((uint32_t)ceil_div(bins->n_vis, kWave)),
-                                                        dim3(kWave), 0, st, bins->vis_rec, bins->inst_off, bins->n_vis, nrec,
-                                                        (const double*)partial, g2d));
-    TIDE_LAUNCH_CHECK("k_reduce_pairs");
-    const CamSet<double> cs = make_camset<double>(cams, n_cams);
-    if (proj->n_pidx > 0) {
-      if (cfg)
-        TIDE_TIMED("adjoint_adam", st, launch_adjoint_adam<double>(pool, proj, cs, g2d, cfg, st));
-      else
-        TIDE_TIMED("adjoint", st, launch_adjoint<double>(pool, proj, cs, g2d, (double*)grad, grad_ld, st));
-    }
-    TIDE_LAUNCH_CHECK("k_adjoint");
-  }
-  return TIDE_OK;
+  return proj->dtype == TIDE_F32
+             ? render_bwd_t<float>(pool, cams, n_cams, proj, bins, fr, bg, d_dimage, grad, grad_ld, cfg, ws, st)
+             : render_bwd_t<double>(pool, cams, n_cams, proj, bins, fr, bg, d_dimage, grad, grad_ld, cfg, ws, st);
 }
 
 static tide_status render_bwd_check(const tide_pool* pool, const tide_camera* cams, int32_t n_cams,

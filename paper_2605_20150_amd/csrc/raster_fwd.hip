@@ -367,60 +367,98 @@ struct PairRectOut {
 };
 
 // Instances of the depth-ordered visible pairs, each pair's tiles in
-// row-major order.  A wave64 workgroup takes 64 consecutive pairs at a time
-// (grid-stride over the pair count read on the device) and walks their
-// contiguous instance range [inst_off[s0], inst_off[s0 + 64])) 64 at a time
-// (coalesced writes); a lane finds its pair by binary search over the 64
-// offsets and its tile from the pair's first tile and width.  Balanced
-// whatever the footprint sizes.  Instances at or past cap are not written
-// (the call then reports the count it needs).  The grid also clears
-// zero[0, n_zero) (the tile ranges, filled in later).
+// row-major order.  A wave64 workgroup takes equal pieces of the instances
+// (grid-stride over the count read on the device), starts at the pair that the
+// offsets' scan marked for the piece, and walks on from there 64 pairs at a
+// time, the next 64 pairs' values loaded meanwhile; a lane finds its pair
+// by binary search over the 64 offsets in LDS and its tile from the pair's
+// first tile and width, so the writes are coalesced.  Split by instances, not
+// by pairs: the nearest pairs come first and cover thousands of tiles each at
+// street level, and a wave that took 64 of them ran long after the rest
+// (20M Gaussians, 4 x 1600x900: 2705 us by pairs, 400 us now; 1M from above,
+// where footprints are even: 37 and 39 us).  Instances at or past cap are not written (the call then reports the count it
+// needs).  The grid also clears zero[0, n_zero) (the tile ranges, filled in
+// later).
+constexpr int kEmitWaves = 32768;       // pieces aimed at: four times what the chip holds at once
+constexpr int64_t kEmitMin = 1 << kMarkShift, kEmitMax = 2048;
 __global__ void __launch_bounds__(64) k_emit(const uint32_t* __restrict__ first, const uint32_t* __restrict__ width,
                                              const uint32_t* __restrict__ vis_rec,
-                                             const uint32_t* __restrict__ inst_off, int64_t nv_max,
-                                             const unsigned long long* __restrict__ d_nvis, int64_t cap, int32_t Tx,
+                                             const uint32_t* __restrict__ inst_off,
+                                             const uint32_t* __restrict__ mark, int64_t nv_max,
+                                             const unsigned long long* __restrict__ d_nvis, int64_t cap,
+                                             const unsigned long long* __restrict__ d_ninst, int32_t Tx,
                                              uint32_t* __restrict__ tkey, uint32_t* __restrict__ inst_rec,
                                              uint32_t* __restrict__ zero, int64_t n_zero) {
   const int lane = threadIdx.x;
   for (int64_t i = (int64_t)blockIdx.x * kWave + lane; i < n_zero; i += (int64_t)gridDim.x * kWave) zero[i] = 0u;
-  const int64_t n_vis = dev_count(nv_max, d_nvis);
+  // pair and instance indices fit 32 bits (a larger count is refused after the
+  // fact; the clamp keeps this kernel in bounds then)
+  const uint32_t n_vis = (uint32_t)dev_count(nv_max, d_nvis);
+  const int64_t n = dev_count(cap < 0xffffffffll ? cap : 0xffffffffll, d_ninst);
+  if (n_vis == 0) return;
+  int64_t piece = (n + kEmitWaves - 1) / kEmitWaves;
+  piece = (piece + kEmitMin - 1) / kEmitMin * kEmitMin;
+  piece = piece < kEmitMin ? kEmitMin : (piece > kEmitMax ? kEmitMax : piece);
   __shared__ uint32_t s_off[kWave + 1];
   __shared__ uint32_t s_rec[kWave], s_first[kWave], s_w[kWave];
-  for (int64_t s0 = (int64_t)blockIdx.x * kWave; s0 < n_vis; s0 += (int64_t)gridDim.x * kWave) {
-    const int np = (int)(n_vis - s0 < kWave ? n_vis - s0 : kWave);
-    if (lane <= np) s_off[lane] = inst_off[s0 + lane];
-    if (lane == 0 && np == kWave) s_off[kWave] = inst_off[s0 + kWave];
-    if (lane < np) {
-      s_rec[lane] = vis_rec[s0 + lane];
-      s_first[lane] = first[s0 + lane];
-      s_w[lane] = width[s0 + lane];
-    }
-    __syncthreads();
-    const uint32_t e0 = s_off[0];
-    const uint32_t e1 = (int64_t)s_off[np] < cap ? s_off[np] : (uint32_t)cap;
-    for (uint32_t e = e0 + (uint32_t)lane; e < e1; e += kWave) {
-      int lo = 0, hi = np;   // s_off[lo] <= e < s_off[hi]
-      while (hi - lo > 1) {
-        const int mid = (lo + hi) >> 1;
-        if (s_off[mid] <= e) lo = mid;
-        else hi = mid;
+  for (int64_t e0 = (int64_t)blockIdx.x * piece; e0 < n; e0 += (int64_t)gridDim.x * piece) {
+    uint32_t e = (uint32_t)e0;
+    const uint32_t e1 = (uint32_t)(e0 + piece < n ? e0 + piece : n);
+    // every window of pairs moves on by at least one, so the walk ends
+    // whatever the offsets hold (after a failed sort)
+    uint32_t s = mark[e0 >> kMarkShift];
+    s = s < n_vis ? s : n_vis - 1;
+    uint32_t o = 0, o_end = 0, r = 0, f = 0, w = 0;
+    auto fetch = [&](uint32_t at) {   // lane's pair at + lane, clamped to the last
+      const uint32_t i = n_vis - at > (uint32_t)lane ? at + lane : n_vis - 1;
+      const uint32_t z = n_vis - at > (uint32_t)kWave ? at + kWave : n_vis;
+      o = inst_off[i];
+      o_end = inst_off[z];
+      r = vis_rec[i];
+      f = first[i];
+      w = width[i];
+    };
+    fetch(s);
+    while (e < e1 && s < n_vis) {
+      const uint32_t np = n_vis - s < (uint32_t)kWave ? n_vis - s : (uint32_t)kWave;
+      __syncthreads();
+      if ((uint32_t)lane < np) {
+        s_off[lane] = o;
+        s_rec[lane] = r;
+        s_first[lane] = f;
+        s_w[lane] = w;
       }
-      const uint32_t k = e - s_off[lo], w = s_w[lo];
-      // row = k / w: below 2^24 from the float reciprocal, corrected by one
-      // step (the estimate is off by less than one: row < 2^16)
-      uint32_t row;
-      if (k < (1u << 24)) {
-        row = (uint32_t)((float)k * __builtin_amdgcn_rcpf((float)w));
-        row = row * w > k ? row - 1u : row;
-        row = (row + 1u) * w <= k ? row + 1u : row;
-      } else {
-        row = k / w;
+      if (lane == 0) s_off[np] = o_end;
+      __syncthreads();
+      const uint32_t we = s_off[np] < e1 ? s_off[np] : e1;
+      if (we < e1 && s + np < n_vis) fetch(s + np);
+      const uint32_t len = we > e ? we - e : 0u;
+      for (uint32_t i = lane; i < len; i += kWave) {
+        const uint32_t x = e + i;
+        uint32_t lo = 0, hi = np;   // s_off[lo] <= x < s_off[hi]
+        while (hi - lo > 1) {
+          const uint32_t mid = (lo + hi) >> 1;
+          if (s_off[mid] <= x) lo = mid;
+          else hi = mid;
+        }
+        const uint32_t k = x - s_off[lo], pw = s_w[lo];
+        // row = k / w: below 2^24 from the float reciprocal, corrected by one
+        // step (the estimate is off by less than one: row < 2^16)
+        uint32_t row;
+        if (k < (1u << 24)) {
+          row = (uint32_t)((float)k * __builtin_amdgcn_rcpf((float)pw));
+          row = row * pw > k ? row - 1u : row;
+          row = (row + 1u) * pw <= k ? row + 1u : row;
+        } else {
+          row = k / pw;
+        }
+        const uint32_t col = k - row * pw;
+        tkey[x] = s_first[lo] + row * (uint32_t)Tx + col;
+        inst_rec[x] = s_rec[lo];
       }
-      const uint32_t col = k - row * w;
-      tkey[e] = s_first[lo] + row * (uint32_t)Tx + col;
-      inst_rec[e] = s_rec[lo];
+      e += len;
+      s += np;
     }
-    __syncthreads();
   }
 }
 
@@ -580,12 +618,14 @@ constexpr int kDepthRounds = 64 / kDepthWaves;
 struct BinLayout {
   uint32_t *vis_off, *ka, *va, *kb, *vb, *inst_off, *tka, *tva, *tkb, *tvb, *inst_rec, *ranges, *order;
   uint32_t *oka, *ova, *okb, *ovb;   // launch-order radix sort (grids beyond kOrderMaxBlocks blocks)
+  uint32_t* mark;                    // per 2^kMarkShift instances, the pair that holds the first
   uint32_t* pwidth;                  // per visible pair in depth order, its rectangle's width
   uint32_t* ctl;                     // control words of the depth sort
   unsigned long long* status;        // its look-back words
   uint32_t* hist;                    // per-tile digit counts of the tile sort
   unsigned long long* tvis;          // per-tile visit counts of the compositing
   unsigned long long *partial, *totals;
+  uint32_t n_mark;
   size_t bytes;
 };
 
@@ -612,6 +652,8 @@ static BinLayout bin_layout(void* ws, int n_cams, int64_t n_pidx, int64_t n_tile
   L.tkb = cv.take<uint32_t>(cap);
   L.tvb = cv.take<uint32_t>(cap);
   L.inst_rec = cv.take<uint32_t>(cap);
+  L.n_mark = (uint32_t)((cap >> kMarkShift) + 1 < (1ll << 26) ? (cap >> kMarkShift) + 1 : (1ll << 26));
+  L.mark = cv.take<uint32_t>(L.n_mark);
   const int64_t ntt = (int64_t)n_cams * n_tiles;
   L.ranges = cv.take<uint32_t>(2 * (size_t)ntt);
   L.order = cv.take<uint32_t>(ntt);
@@ -975,7 +1017,8 @@ extern "C" tide_status tide_bin_sort(const tide_proj* proj, int32_t tiles_x, int
     tail.copy_src = L.totals;
     tail.copy_dst = slot.host;
     tail.copy_n = 4;
-    scan_exclusive(ArrayIn{L.vis_off}, nv, L.inst_off, L.partial, &L.totals[2], st, &L.totals[0], tail);
+    scan_to(ArrayIn{L.vis_off}, nv, OffsetsMarkOut{L.inst_off, L.mark, L.n_mark}, L.partial, &L.totals[2], st,
+            &L.totals[0], tail);
   }
   TIDE_LAUNCH_CHECK("instance scan");
   TIDE_HIP(hipEventRecord(slot.ev, st));
@@ -983,10 +1026,10 @@ extern "C" tide_status tide_bin_sort(const tide_proj* proj, int32_t tiles_x, int
   //    the tile ranges)
   const int64_t nr = 2 * (int64_t)V * nt;
   {
-    const int64_t chunks = ceil_div(nv > 0 ? nv : 1, kWave);
-    TIDE_TIMED("emit", st, hipLaunchKernelGGL(k_emit, dim3((uint32_t)(chunks < 32768 ? chunks : 32768)), dim3(kWave), 0,
-                                              st, pfirst, L.pwidth, vrec, L.inst_off, nv, &L.totals[0], cap, tiles_x,
-                                              L.tka, L.inst_rec, L.ranges, nr));
+    const int64_t pieces = ceil_div(cap > 0 ? cap : 1, kEmitMin);
+    TIDE_TIMED("emit", st, hipLaunchKernelGGL(k_emit, dim3((uint32_t)(pieces < kEmitWaves ? pieces : kEmitWaves)),
+                                              dim3(kWave), 0, st, pfirst, L.pwidth, vrec, L.inst_off, L.mark, nv, &L.totals[0],
+                                              cap, &L.totals[2], tiles_x, L.tka, L.inst_rec, L.ranges, nr));
   }
   TIDE_LAUNCH_CHECK("k_emit");
   // 6. stable sort by tile; values are emission indices (histogram, scan
