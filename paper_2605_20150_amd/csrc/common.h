@@ -78,6 +78,10 @@ struct Mth<float> {
   __device__ static float log(float x) { return __logf(x); }
   __device__ static float ceil(float x) { return ceilf(x); }
   __device__ static float floor(float x) { return floorf(x); }
+  __device__ static float log_fast(float x) { return 0.69314718f * __builtin_amdgcn_logf(x); }
+  __device__ static float max(float a, float b) { return fmaxf(a, b); }
+  __device__ static float clamp(float x, float lo, float hi) { return __builtin_amdgcn_fmed3f(x, lo, hi); }
+  __device__ static float fma(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
 };
 
 template <>
@@ -89,6 +93,10 @@ struct Mth<double> {
   __device__ static double log(double x) { return ::log(x); }
   __device__ static double ceil(double x) { return ::ceil(x); }
   __device__ static double floor(double x) { return ::floor(x); }
+  __device__ static double log_fast(double x) { return ::log(x); }
+  __device__ static double max(double a, double b) { return fmax(a, b); }
+  __device__ static double clamp(double x, double lo, double hi) { return fmin(fmax(x, lo), hi); }
+  __device__ static double fma(double a, double b, double c) { return __builtin_fma(a, b, c); }
 };
 
 // ------------------------------------------------------------ wave64
@@ -98,6 +106,10 @@ __device__ inline uint64_t lanemask_lt() {
   const uint32_t lane = __lane_id();
   return lane == 0 ? 0ull : (~0ull >> (64 - lane));
 }
+
+// This lane's bit of a wave-uniform mask, as a condition (the mask itself serves
+// as the select's operand: no vector instruction).
+__device__ __forceinline__ bool lane_bit(uint64_t mask) { return __builtin_amdgcn_inverse_ballot_w64(mask); }
 
 // Sum over the 64 lanes; the result is valid in every lane.
 template <typename T>

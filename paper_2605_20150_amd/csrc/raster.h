@@ -155,13 +155,14 @@ struct Ex<double> {
 // offset, adx2 = Ah dx dx and bdx = Bh dx; then power = adx2 + bdx dy +
 // Ch dy dy.  ok is false when the entry is skipped (power > 0 or
 // alpha < 1/255); G = exp(power / k), araw = opacity G, alpha = min(0.99, araw).
+// The fused operations are written out, so that every kernel rounds the same
+// way whatever surrounds the call.
 template <typename T>
-__device__ __forceinline__ void entry_alpha_tests(T adx2, T bdx, T Ch, T op, T dy, T& G, T& araw, T& alpha,
-                                                  bool& in_power, bool& in_alpha) {
-  const T power = adx2 + dy * (bdx + Ch * dy);
+__device__ __forceinline__ void entry_alpha_tests(T adx2, T bdx, T Ch, T op, T dy, T& G, T& araw, bool& in_power,
+                                                  bool& in_alpha) {
+  const T power = Mth<T>::fma(dy, Mth<T>::fma(Ch, dy, bdx), adx2);
   G = Ex<T>::eval(power);
   araw = op * G;
-  alpha = araw < (T)0.99 ? araw : (T)0.99;
   in_power = power <= (T)0;
   // alpha >= 1/255 exactly when araw >= 1/255 (0.99 > 1/255; a NaN araw
   // comes from a NaN power, which fails in_power)
@@ -177,36 +178,46 @@ __device__ __forceinline__ double alpha_clamped(double araw, bool below) {
   return __longlong_as_double(below ? __double_as_longlong(araw) : __double_as_longlong(0.99));
 }
 
+// Test of one list entry against a box of W x H pixels whose first centre is
+// (x0 + 0.5, y0 + 0.5), conservative: false only when no pixel centre of the box
+// can take the entry, i.e. when opacity * G < 1/255 at every centre,
+// G = exp(-Q/2), Q = A dx^2 + 2 B dx dy + C dy^2 (the conic is positive
+// definite).  The minimum of Q over the continuous box of the pixel centres
+// bounds it over the centres: 0 if the mean is inside, else the least of the
+// four edge minima (on an edge, Q is a 1-D quadratic minimised at the clamped
+// stationary point).  A slack of 1e-3 (relative and absolute) covers the
+// rounding of this test and of the per-pixel one.
+// box_prepare forms what does not depend on the box, once per entry: the slopes
+// of the stationary points, -B/A and -B/C, and the bound on Q/2 in the scaled
+// conic's units; box_may_take takes the scaled conic of entry_alpha_tests
+// (Ah = -A k/2, Bh = -B k, Ch = -C k/2), in which -k Q / 2 = Ah dx^2 + Bh dx dy +
+// Ch dy^2.  (Reciprocals within an ulp: a point of the edge that is off by that
+// still bounds Q within the slack.)
 template <typename T>
-__device__ __forceinline__ bool entry_alpha(T adx2, T bdx, T Ch, T op, T dy, T& G, T& araw, T& alpha) {
-  bool in_power, in_alpha;
-  entry_alpha_tests<T>(adx2, bdx, Ch, op, dy, G, araw, alpha, in_power, in_alpha);
-  return in_power && in_alpha;
+__device__ __forceinline__ void box_prepare(T A, T B, T C, T op, T& ka, T& kc, T& lim) {
+  ka = -B * Mth<T>::rcp_fast(A);
+  kc = -B * Mth<T>::rcp_fast(C);
+  lim = -(T)(Ex<T>::k / (1.0 - 1e-3)) * (Mth<T>::log_fast((T)255 * op) + (T)1e-3);
 }
-
-// Tile-level test of one list entry, conservative: false only when no pixel
-// centre of tile (tx, ty) can take the entry, i.e. when opacity * G < 1/255
-// at every centre, G = exp(-Q/2), Q = A dx^2 + 2 B dx dy + C dy^2 (the conic
-// is positive definite).  The minimum of Q over the continuous box of the
-// tile's pixel centres bounds it over the centres: 0 if the mean is inside,
-// else the least of the four edge minima (on an edge, Q is a 1-D quadratic
-// minimised at the clamped stationary point).  A slack of 1e-3 (relative and
-// absolute) covers the rounding of this test and of the per-pixel one.
+template <int W, int H, typename T>
+__device__ __forceinline__ bool box_may_take(T u, T v, T Ah, T Bh, T Ch, T ka, T kc, T lim, int x0, int y0) {
+  const T xa = (T)x0 + (T)0.5 - u, xb = xa + (T)(W - 1);
+  const T ya = (T)y0 + (T)0.5 - v, yb = ya + (T)(H - 1);
+  auto cl = [](T x, T lo, T hi) { return Mth<T>::clamp(x, lo, hi); };
+  auto p = [&](T dx, T dy) { return dx * (Ah * dx + Bh * dy) + Ch * dy * dy; };
+  const T e0 = p(xa, cl(kc * xa, ya, yb)), e1 = p(xb, cl(kc * xb, ya, yb));
+  const T e2 = p(cl(ka * ya, xa, xb), ya), e3 = p(cl(ka * yb, xa, xb), yb);
+  const T best = Mth<T>::max(Mth<T>::max(e0, e1), Mth<T>::max(e2, e3));
+  const bool inside = xa <= (T)0 && xb >= (T)0 && ya <= (T)0 && yb >= (T)0;
+  return inside ? lim <= (T)0 : !(best < lim);
+}
 template <typename T>
 __device__ __forceinline__ bool tile_may_take(T u, T v, T A, T B, T C, T op, int tx, int ty) {
-  const T xa = (T)(kTile * tx) + (T)0.5 - u, xb = xa + (T)(kTile - 1);
-  const T ya = (T)(kTile * ty) + (T)0.5 - v, yb = ya + (T)(kTile - 1);
-  T qmin = 0;
-  if (!(xa <= (T)0 && xb >= (T)0 && ya <= (T)0 && yb >= (T)0)) {
-    auto q = [&](T dx, T dy) { return A * dx * dx + (T)2 * B * dx * dy + C * dy * dy; };
-    auto cl = [](T x, T lo, T hi) { return x < lo ? lo : (x > hi ? hi : x); };
-    const T e0 = q(xa, cl(-B * xa / C, ya, yb)), e1 = q(xb, cl(-B * xb / C, ya, yb));
-    const T e2 = q(cl(-B * ya / A, xa, xb), ya), e3 = q(cl(-B * yb / A, xa, xb), yb);
-    qmin = e0 < e1 ? e0 : e1;
-    qmin = qmin < e2 ? qmin : e2;
-    qmin = qmin < e3 ? qmin : e3;
-  }
-  return (T)0.5 * qmin * (T)(1.0 - 1e-3) <= Mth<T>::log((T)255 * op) + (T)1e-3;
+  T ka, kc, lim;
+  box_prepare<T>(A, B, C, op, ka, kc, lim);
+  const T k = (T)Ex<T>::k;
+  return box_may_take<kTile, kTile, T>(u, v, (T)-0.5 * k * A, -k * B, (T)-0.5 * k * C, ka, kc, lim, kTile * tx,
+                                       kTile * ty);
 }
 
 // Wave64 sum with DPP row shifts and row broadcasts; the total lands in

@@ -156,9 +156,9 @@ __global__ void __launch_bounds__(64) k_render_bwd(const uint32_t* __restrict__ 
       uint64_t qm[4], hit_m = 0;   // per pixel row q, the lanes whose pixel takes the entry
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
-        T araw, alpha;
+        T araw;
         bool in_power, in_alpha;
-        entry_alpha_tests<T>(adx2, bdx, Ch, op, fyp[q] - v, Gq[q], araw, alpha, in_power, in_alpha);
+        entry_alpha_tests<T>(adx2, bdx, Ch, op, fyp[q] - v, Gq[q], araw, in_power, in_alpha);
         const bool before_last = pos < lst[q];
         okq[q] = in_power && in_alpha && before_last;
         qm[q] = __ballot(in_power) & __ballot(in_alpha) & __ballot(before_last);

@@ -677,145 +677,182 @@ static BinLayout bin_layout(void* ws, int n_cams, int64_t n_pidx, int64_t n_tile
 }
 
 // ------------------------------------------------------------- compositing
-// One wave64 per 16x16 tile; lane l owns the four pixels of column l % 16,
-// rows l / 16 + {0, 4, 8, 12}.  The tile's list is streamed through LDS in
-// batches of 64 records and read back as broadcasts.  The per-pixel update is
-// branch-free (selects on the skip / stop / contribute predicates), and the
-// terms that depend only on the lane's column are formed once per entry and
-// shared by its four pixels.
+// One workgroup of four waves per 16x16 tile, a wave per 8x8 quadrant, a pixel
+// per lane.  The tile's list is streamed through LDS in batches of kFwdBatch
+// records, the next batch's records on their way meanwhile; each wave then tests
+// the batch against its own quadrant, one entry per lane, and walks the entries
+// that some of its pixel centres may take.  Issue of vector instructions bounds
+// the kernel where tiles are many, and the chain of a single tile's list where
+// they are few.  Quadrants cut both: a small footprint meets one or two of the
+// four (a wave per whole tile, four pixels per lane, did the per-pixel work of
+// all), and a long list is walked by four waves at once.  The walk takes three
+// entries at a time: their alphas do not depend on each other, only the updates
+// of the transmittance follow in order.
+// Before (one wave per tile) and now: 4 x 1920x1080, 1M Gaussians 605 and 526
+// us; 1237x823, 300k 650 and 167 us; 64x64 83 and 21 us.  Footprints that cover
+// whole tiles gain nothing from quadrants: street level, 20M, 320 and 394 us of
+// an 18 ms step.  One entry at a time 566 us (aerial), two 535, four 548;
+// batches of 128 the same.  One wave per tile that skips quadrants by branches:
+// 1012 us.
+constexpr int kFwdBatch = 64, kFwdGroup = 3;
+constexpr int kFwdSlots = kFwdBatch + kWave;   // the arrays keep a multiple of 64 apart: pairs of reads fuse
+
 template <typename T>
-__global__ void __launch_bounds__(64) k_render_fwd(const uint32_t* __restrict__ order,
-                                                   const uint32_t* __restrict__ ranges,
-                                                   const uint32_t* __restrict__ inst_e,
-                                                   const uint32_t* __restrict__ inst_rec, const T* __restrict__ rec,
-                                                   int32_t Tx, int32_t Ty, int32_t W, int32_t H, T bg0, T bg1,
-                                                   T bg2, T* __restrict__ image, T* __restrict__ tfin,
-                                                   uint32_t* __restrict__ last_out,
-                                                   unsigned long long* __restrict__ tile_visits) {
+__global__ void __launch_bounds__(256) k_render_fwd(const uint32_t* __restrict__ order,
+                                                    const uint32_t* __restrict__ ranges,
+                                                    const uint32_t* __restrict__ inst_e,
+                                                    const uint32_t* __restrict__ inst_rec, const T* __restrict__ rec,
+                                                    int32_t Tx, int32_t Ty, int32_t W, int32_t H, T bg0, T bg1, T bg2,
+                                                    T* __restrict__ image, T* __restrict__ tfin,
+                                                    uint32_t* __restrict__ last_out,
+                                                    unsigned long long* __restrict__ tile_visits) {
+  constexpr int kQ = kTile / 2;
   const int nt = Tx * Ty;
   const int g = (int)order[blockIdx.x];
   const int c = g / nt, t = g - c * nt;
   const int tx = t % Tx, ty = t / Tx;
-  const int lane = threadIdx.x;
-  const int px = tx * kTile + (lane & 15);
-  const int py0 = ty * kTile + (lane >> 4);
+  const int lane = __lane_id(), w = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+  const int qx = tx * kTile + (w & 1) * kQ, qy = ty * kTile + (w >> 1) * kQ;   // the wave's quadrant
+  const int px = qx + (lane & 7), py = qy + (lane >> 3);
   const T fxp = (T)px + (T)0.5;
+  const bool in = px < W && py < H;
   // A pixel that stops (or lies outside the image) moves its row to
   // +infinity, where no entry reaches it, so the per-entry work needs no
   // liveness test; Tr then keeps its final T.
   const T kGone = __builtin_inf();
-  T fyp[4], Tr[4], C0[4], C1[4], C2[4];
-  uint32_t lst[4];
-  // live pixels of the wave; every entry reached counts them as visits
-  uint32_t nlive = 0;
-#pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    const bool in = px < W && py0 + 4 * q < H;
-    fyp[q] = in ? (T)(py0 + 4 * q) + (T)0.5 : kGone;
-    Tr[q] = 1;
-    C0[q] = C1[q] = C2[q] = 0;
-    lst[q] = 0;
-    nlive += (uint32_t)__popcll(__ballot(in));
-  }
-  unsigned long long nvis = 0;   // wave-uniform: live pixels summed over entries
+  T fyp = in ? (T)py + (T)0.5 : kGone, Tr = 1, C0 = 0, C1 = 0, C2 = 0;
+  uint32_t lst = 0;
   const uint32_t start = ranges[2 * g], end = ranges[2 * g + 1];
-  __shared__ T s_u[64], s_v[64], s_A[64], s_B[64], s_C[64], s_o[64], s_r[64], s_g[64], s_b[64];
+  uint32_t vis = in ? end - start : 0;   // entries the pixel visits: all, unless it stops
+  uint32_t nlive = (uint32_t)__popcll(__ballot(in));
+
+  // entry fields; slot kFwdBatch is one that no pixel takes (opacity 0), which
+  // fills up the last group of a walk
+  __shared__ T s_u[kFwdSlots], s_v[kFwdSlots], s_A[kFwdSlots], s_B[kFwdSlots], s_C[kFwdSlots],
+      s_o[kFwdSlots], s_r[kFwdSlots], s_g[kFwdSlots], s_b[kFwdSlots], s_ka[kFwdBatch], s_kc[kFwdBatch], s_lim[kFwdBatch];
+  __shared__ uint32_t s_live[4];
   const T ks = (T)Ex<T>::k;
-  bool any = nlive != 0;
-  for (uint32_t b0 = start; b0 < end && any; b0 += 64) {
-    const uint32_t j = b0 + lane;
-    bool may = false;
-    if (j < end) {
-      const T* q = rec + (int64_t)inst_rec[inst_e[j]] * kRec;
-      s_u[lane] = q[0]; s_v[lane] = q[1];
-      s_A[lane] = (T)-0.5 * ks * q[2]; s_B[lane] = -ks * q[3]; s_C[lane] = (T)-0.5 * ks * q[4];
-      s_o[lane] = q[5]; s_r[lane] = q[6]; s_g[lane] = q[7]; s_b[lane] = q[8];
-      // entries whose footprint misses every pixel centre of the tile at
-      // alpha >= 1/255 (about 40 % of the aerial scene's instances) are
-      // passed over without any per-pixel work
-      may = tile_may_take<T>(q[0], q[1], q[2], q[3], q[4], q[5], tx, ty);
-    }
-    // the batch's entries that some pixel centre may take, one bit each: the
-    // walk below visits only those, and the others cost nothing
-    uint64_t rest = __ballot(may);
-    __syncthreads();
-    const int nb = (int)(end - b0 < 64 ? end - b0 : 64);
-    int counted = 0;   // entries of the batch whose visits are in nvis
-    while (rest != 0) {
-      const int k = __builtin_ctzll(rest);
-      rest &= rest - 1;
-      // every live pixel visits entries counted..k
-      nvis += (unsigned long long)nlive * (unsigned long long)(k + 1 - counted);
-      counted = k + 1;
-      const T v = s_v[k], Ch = s_C[k], op = s_o[k];
-      const T cr = s_r[k], cg = s_g[k], cb = s_b[k];
-      const T dx = fxp - s_u[k];
-      const T adx2 = s_A[k] * dx * dx, bdx = s_B[k] * dx;
-      const uint32_t idx = b0 - start + (uint32_t)k + 1;
-      // Alphas first: when no pixel takes the entry (the tile test is
-      // conservative, and pixels stop), the update below would change
-      // nothing, and the wave skips it.  Each comparison is balloted on its
-      // own and the masks are combined on the scalar unit (a ballot of a
-      // combined condition costs two vector instructions).
-      T al[4];
-      bool ps[4];
-      uint64_t pm[4], take_m = 0;
+  const int tid = threadIdx.x;
+  if (tid == 0) {
+    s_u[kFwdBatch] = s_v[kFwdBatch] = s_A[kFwdBatch] = s_B[kFwdBatch] = s_C[kFwdBatch] = s_o[kFwdBatch] = 0;
+    s_r[kFwdBatch] = s_g[kFwdBatch] = s_b[kFwdBatch] = 0;
+  }
+  // thread tid < kFwdBatch stages entry tid of each batch: f holds the fields
+  // of the batch to come, r_n the record index of the one after
+  const bool stages = tid < kFwdBatch;
+  T f[9];
+  uint32_t r_n = 0;
+  auto load = [&](uint32_t r) {
+    const T* q = rec + (int64_t)r * kRec;
 #pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        T G, araw;
-        bool in_power, in_alpha;
-        entry_alpha_tests<T>(adx2, bdx, Ch, op, fyp[q] - v, G, araw, al[q], in_power, in_alpha);
-        ps[q] = in_power && in_alpha;
-        pm[q] = __ballot(in_power) & __ballot(in_alpha);
-        take_m |= pm[q];
-      }
-      if (take_m == 0) continue;
-      uint32_t nstop = 0;
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        if (pm[q] == 0) continue;   // no pixel of row group q takes the entry: nothing changes
-        const T alpha = al[q];
-        const bool pass = ps[q];
-        const T wr = alpha * Tr[q];
-        const T tn = Tr[q] - wr;   // T (1 - alpha)
-        const bool low = tn < (T)1e-4;
-        const bool stop = pass && low;
-        const bool take = pass && !low;
-        const T w = take ? wr : (T)0;
-        C0[q] += cr * w; C1[q] += cg * w; C2[q] += cb * w;
-        Tr[q] = take ? tn : Tr[q];
-        fyp[q] = stop ? kGone : fyp[q];
-        lst[q] = take ? idx : lst[q];
-        nstop += (uint32_t)__popcll(pm[q] & __ballot(low));
-      }
-      nlive -= nstop;
-      if (nlive == 0) { any = false; break; }
+    for (int m = 0; m < 9; ++m) f[m] = q[m];
+  };
+  if (stages) {
+    if (end - start > (uint32_t)tid) load(inst_rec[inst_e[start + tid]]);
+    if (end - start > (uint32_t)(kFwdBatch + tid)) r_n = inst_rec[inst_e[start + kFwdBatch + tid]];
+  }
+  for (uint32_t b0 = start; b0 < end; b0 += kFwdBatch) {
+    const uint32_t left = end - b0;
+    if (stages && left > (uint32_t)tid) {
+      s_u[tid] = f[0]; s_v[tid] = f[1];
+      s_A[tid] = (T)-0.5 * ks * f[2]; s_B[tid] = -ks * f[3]; s_C[tid] = (T)-0.5 * ks * f[4];
+      box_prepare<T>(f[2], f[3], f[4], f[5], s_ka[tid], s_kc[tid], s_lim[tid]);
+      s_o[tid] = f[5]; s_r[tid] = f[6]; s_g[tid] = f[7]; s_b[tid] = f[8];
     }
-    nvis += (unsigned long long)nlive * (unsigned long long)(nb - counted);
     __syncthreads();
+    if (stages) {
+      if (left > (uint32_t)(kFwdBatch + tid)) load(r_n);
+      if (left > (uint32_t)(2 * kFwdBatch + tid)) r_n = inst_rec[inst_e[b0 + 2 * kFwdBatch + tid]];
+    }
+#pragma unroll
+    for (int h = 0; h < kFwdBatch; h += kWave) {
+      if (nlive == 0 || left <= (uint32_t)h) break;
+      const int k0 = h + lane;
+      bool may = false;
+      // entries whose footprint misses every pixel centre of the quadrant at
+      // alpha >= 1/255 are passed over without any per-pixel work
+      if (left > (uint32_t)k0)
+        may = box_may_take<kQ, kQ, T>(s_u[k0], s_v[k0], s_A[k0], s_B[k0], s_C[k0], s_ka[k0], s_kc[k0], s_lim[k0], qx, qy);
+      uint64_t rest = __ballot(may);
+      while (rest != 0) {
+        int k[kFwdGroup];
+#pragma unroll
+        for (int i = 0; i < kFwdGroup; ++i) {
+          k[i] = rest != 0 ? h + (int)__builtin_ctzll(rest) : kFwdBatch;
+          rest &= rest - 1;   // 0 stays 0
+        }
+        // Alphas first: when no pixel takes an entry (the quadrant test is
+        // conservative, and pixels stop), its update would change nothing.
+        // Each comparison is balloted on its own and the masks are combined
+        // on the scalar unit (a ballot of a combined condition costs two
+        // vector instructions).
+        T araw[kFwdGroup];
+        uint64_t pm[kFwdGroup], any = 0;   // per entry, the lanes whose pixel takes it
+#pragma unroll
+        for (int i = 0; i < kFwdGroup; ++i) {
+          const T dx = fxp - s_u[k[i]], dy = fyp - s_v[k[i]];
+          T G;
+          bool in_power, in_alpha;
+          entry_alpha_tests<T>(s_A[k[i]] * dx * dx, s_B[k[i]] * dx, s_C[k[i]], s_o[k[i]], dy, G, araw[i], in_power,
+                               in_alpha);
+          pm[i] = __ballot(in_power) & __ballot(in_alpha);
+          any |= pm[i];
+        }
+        if (any == 0) continue;
+#pragma unroll
+        for (int i = 0; i < kFwdGroup; ++i) {
+          if (pm[i] == 0) continue;
+          // min(araw, 0.99) where the entry is taken (araw >= 1/255 there)
+          const T alpha = Mth<T>::clamp(araw[i], (T)0, (T)0.99);
+          const T wr = alpha * Tr;
+          const T tn = Mth<T>::fma(-alpha, Tr, Tr);   // T (1 - alpha)
+          const uint32_t idx = b0 - start + (uint32_t)k[i] + 1;
+          const uint64_t sm = pm[i] & __ballot(tn < (T)1e-4);
+          const bool take = lane_bit(pm[i] & ~sm);
+          const T wt = take ? wr : (T)0;
+          C0 = Mth<T>::fma(s_r[k[i]], wt, C0);
+          C1 = Mth<T>::fma(s_g[k[i]], wt, C1);
+          C2 = Mth<T>::fma(s_b[k[i]], wt, C2);
+          Tr = take ? tn : Tr;
+          lst = take ? idx : lst;
+          if (sm != 0) {   // some pixel stops here: the entry is its last visit
+            const bool stop = lane_bit(sm);
+            vis = stop ? idx : vis;
+            fyp = stop ? kGone : fyp;
+            nlive -= (uint32_t)__popcll(sm);
+#pragma unroll
+            for (int j = i + 1; j < kFwdGroup; ++j) pm[j] &= ~sm;   // tested before the stop
+          }
+        }
+        if (nlive == 0) break;
+      }
+    }
+    if (lane == 0) s_live[w] = nlive;
+    __syncthreads();
+    if ((s_live[0] | s_live[1] | s_live[2] | s_live[3]) == 0) break;
   }
   const int64_t HW = (int64_t)H * W;
-  unsigned long long nback = 0;   // entries the backward walks for this lane's pixels
-#pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    const int py = py0 + 4 * q;
-    if (px < W && py < H) {
-      const int64_t p = (int64_t)py * W + px;
-      nback += lst[q];
-      const T tf = Tr[q];
-      image[((int64_t)c * 3 + 0) * HW + p] = C0[q] + tf * bg0;
-      image[((int64_t)c * 3 + 1) * HW + p] = C1[q] + tf * bg1;
-      image[((int64_t)c * 3 + 2) * HW + p] = C2[q] + tf * bg2;
-      tfin[(int64_t)c * HW + p] = tf;
-      last_out[(int64_t)c * HW + p] = lst[q];
-    }
+  if (in) {
+    const int64_t p = (int64_t)py * W + px;
+    image[((int64_t)c * 3 + 0) * HW + p] = Mth<T>::fma(Tr, bg0, C0);
+    image[((int64_t)c * 3 + 1) * HW + p] = Mth<T>::fma(Tr, bg1, C1);
+    image[((int64_t)c * 3 + 2) * HW + p] = Mth<T>::fma(Tr, bg2, C2);
+    tfin[(int64_t)c * HW + p] = Tr;
+    last_out[(int64_t)c * HW + p] = lst;
   }
-  // per-tile counts, summed per view by k_sum_visits (no same-address
-  // atomics: those cross the XCDs' separate L2s)
-  nback = wave_sum(nback);
+  // per-tile counts (entries the pixels visit, and entries the backward walks),
+  // summed per view by k_sum_visits (no same-address atomics: those cross the
+  // XCDs' separate L2s)
+  const uint64_t nv = wave_sum((uint64_t)vis), nb = wave_sum((uint64_t)lst);
+  __shared__ unsigned long long s_vis[4], s_back[4];
   if (lane == 0) {
-    tile_visits[g] = nvis;
-    tile_visits[gridDim.x + g] = nback;
+    s_vis[w] = nv;
+    s_back[w] = nb;
+  }
+  __syncthreads();
+  if (tid == 0) {
+    tile_visits[g] = s_vis[0] + s_vis[1] + s_vis[2] + s_vis[3];
+    tile_visits[gridDim.x + g] = s_back[0] + s_back[1] + s_back[2] + s_back[3];
   }
 }
 
@@ -1111,11 +1148,11 @@ extern "C" tide_status tide_render_fwd(const tide_proj* proj, const tide_bins* b
   hipStream_t st = (hipStream_t)stream;
   const uint32_t grid = (uint32_t)(bins->n_cams * bins->tiles_x * bins->tiles_y);
   if (proj->dtype == TIDE_F32)
-    TIDE_TIMED("render_fwd", st, hipLaunchKernelGGL(k_render_fwd<float>, dim3(grid), dim3(64), 0, st, bins->tile_order, bins->ranges, bins->inst_e, bins->inst_rec,
+    TIDE_TIMED("render_fwd", st, hipLaunchKernelGGL(k_render_fwd<float>, dim3(grid), dim3(256), 0, st, bins->tile_order, bins->ranges, bins->inst_e, bins->inst_rec,
                        (const float*)proj->rec, bins->tiles_x, bins->tiles_y, fr->width, fr->height, bg[0], bg[1],
                        bg[2], (float*)fr->image, (float*)fr->t_final, fr->last, bins->tile_visits));
   else
-    TIDE_TIMED("render_fwd", st, hipLaunchKernelGGL(k_render_fwd<double>, dim3(grid), dim3(64), 0, st, bins->tile_order, bins->ranges, bins->inst_e,
+    TIDE_TIMED("render_fwd", st, hipLaunchKernelGGL(k_render_fwd<double>, dim3(grid), dim3(256), 0, st, bins->tile_order, bins->ranges, bins->inst_e,
                        bins->inst_rec, (const double*)proj->rec, bins->tiles_x, bins->tiles_y, fr->width,
                        fr->height, (double)bg[0], (double)bg[1], (double)bg[2], (double*)fr->image,
                        (double*)fr->t_final, fr->last, bins->tile_visits));
