@@ -43,3 +43,30 @@ def test_image_contributors_and_gradient(width, height, n, logit):
         assert not gd.any() and not want.any()
     else:
         assert np.linalg.norm(gd - want) <= 1e-10 * np.linalg.norm(want)
+
+
+@pytest.mark.parametrize("dtype,rtol", [(torch.float32, 2e-4), (torch.float64, 5e-13)])
+@pytest.mark.parametrize("n", [25, 400])
+def test_backward_of_few_and_of_many_tiles(n, dtype, rtol):
+    """The two backward compositing kernels (four waves a tile in small grids, one
+    in large ones: over 5120 tiles) form every entry's sums by the same operations
+    in the same order: 8 views of 675 tiles, one with a dL/dimage and the others
+    without, give that view's gradient.  What differs is the order in which a
+    Gaussian's tiles are added (64 at a time in a scan, so at most 6 + 12
+    roundings), of terms that may cancel to a hundredth."""
+    print(f"case: {n} Gaussians, {dtype}", flush=True)
+    w, h, m = 425, 391, 8
+    th = torch.tensor(synth.dense_scene(n, 44, extent=0.3, logscale_mu=-1.5, logscale_sigma=0.6), device="cuda",
+                      dtype=dtype)
+    cams = [synth.look_at((2.5, 0.3, 0.4 + 0.1 * i), (0, 0, 0), (0, 0, 1), w, h, 350.0) for i in range(m)]
+    rast = Rasterizer("cuda")
+    pool = Pool.from_dense(th, 256)
+    dimg = torch.tensor(np.random.Generator(np.random.PCG64(45)).normal(size=(1, 3, h, w)), device="cuda", dtype=dtype)
+    got = []
+    for views in (1, m):
+        d = torch.zeros((views, 3, h, w), device="cuda", dtype=dtype)
+        d[0] = dimg[0]
+        proj, bins, fr = rast.forward(pool, cams[:views])
+        got.append(dense_grad(proj, rast.backward(pool, cams[:views], proj, bins, fr, d), n).cpu())
+    assert got[0].abs().max() > 0
+    assert (got[0] - got[1]).norm() <= rtol * got[0].norm()
