@@ -16,15 +16,34 @@ namespace tide {
 
 constexpr int kHalo = 5, kTaps = 2 * kHalo + 1;
 constexpr int kSpan = kWave + 2 * kHalo;   // 74 staged columns
-// Ring turns per wave and the output rows they give (11 turns - 10 halo
-// rows).  Set for 1080-row frames: the forward's 11 strips of 100 rows are
-// 3960 waves, one round at its four waves per SIMD; the backward (68 VGPRs)
-// does best with 14 strips of 78 rows (measured: 100 rows 204 us against
-// 45 rows 213 us for the forward, 78 rows 164 us against 181 us for the
-// backward, 4 x 3 x 1080 x 1920).
-constexpr int kTurnsFwd = 10, kTurnsBwd = 8;
-constexpr int rows_of(int turns) { return kTaps * turns - 2 * kHalo; }
-constexpr int kRowsFwd = rows_of(kTurnsFwd), kRowsBwd = rows_of(kTurnsBwd);
+// A wave's output rows come from full turns of its register ring (11 turns - 10
+// halo rows), and the launch takes the fewest turns, from 2 up, with which all
+// its waves run at a time: a wave's rows are a serial chain of about 0.6 us each,
+// so shorter strips end sooner until the halo rows (10 a strip) outweigh it or a
+// second round of waves begins.  Waves that run at a time: 4 per SIMD in the
+// forward (its registers), 5 in the backward (7 fit, but past 5 the memory is
+// busy); half of that, 2 and 3, in FP64.  The most turns are set by the largest
+// frames: 100 output rows a wave in the forward (204 us against 213 us with 45 rows) and
+// 78 in the backward (164 us against 181 us with 100), 4 x 3 x 1080 x 1920.
+// Forward + backward, us, always the most turns -> this rule (turns):
+//   1 x 64x64      57 + 53 -> 15 + 17 (2, 2)     4 x 800x450    80 + 67 -> 43 + 39 (3, 3)
+//   2 x 979x546    79 + 67 -> 37 + 34 (3, 2)     1 x 1920x1080  84 + 73 -> 48 + 48 (4, 3)
+//   2 x 1920x1080 105 + 87 -> 89 + 79 (6, 5)     4 x 1600x900  131 + 113 -> 125 + 111 (8, 6)
+constexpr int kMaxTurnsFwd = 10, kMaxTurnsBwd = 8;
+__host__ __device__ constexpr int rows_of(int turns) { return kTaps * turns - 2 * kHalo; }
+struct Turns {
+  int fwd, bwd;
+  Turns(int32_t n_views, int32_t height, int32_t width, int32_t dtype) {
+    const int64_t strips = 3 * (int64_t)n_views * ceil_div(width, kWave), simds = 4 * 256;
+    auto fewest = [&](int most, int64_t waves) {
+      int t = 2;
+      while (t < most && strips * ceil_div(height, rows_of(t)) > waves) ++t;
+      return t;
+    };
+    fwd = fewest(kMaxTurnsFwd, simds * (dtype == TIDE_F64 ? 2 : 4));
+    bwd = fewest(kMaxTurnsBwd, simds * (dtype == TIDE_F64 ? 3 : 5));
+  }
+};
 
 template <typename T>
 struct Win {
@@ -37,7 +56,7 @@ struct Win {
 // part[wave][2] for a fixed-order final sum.
 template <typename T>
 __global__ void __launch_bounds__(kWave) k_ssim_fwd(const T* __restrict__ X, const T* __restrict__ Y, int32_t H,
-                                                    int32_t W, Win<T> win, T* __restrict__ dmaps,
+                                                    int32_t W, Win<T> win, int turns, T* __restrict__ dmaps,
                                                     double* __restrict__ part) {
   __shared__ T sx[2][kSpan], sy[2][kSpan];
   const int lane = threadIdx.x;
@@ -49,7 +68,7 @@ __global__ void __launch_bounds__(kWave) k_ssim_fwd(const T* __restrict__ X, con
   const int ca = c - kHalo;                     // column staged in slot lane
   const int cb = c + kWave - kHalo;             // column staged in slot 64 + lane (lane < 10)
   const bool ina = ca >= 0 && ca < W, inb = lane < 2 * kHalo && cb < W, inc = c < W;
-  const int r0 = blockIdx.y * kRowsFwd;
+  const int rows = rows_of(turns), r0 = blockIdx.y * rows;
   T xa, ya, xb, yb;   // the next input row
   auto fetch = [&](int ir) {
     const bool rin = ir >= 0 && ir < H;
@@ -63,7 +82,7 @@ __global__ void __launch_bounds__(kWave) k_ssim_fwd(const T* __restrict__ X, con
   T ring[kTaps][5];
   const T C1 = (T)1e-4, C2 = (T)9e-4;
   double l1 = 0, ss = 0;
-  for (int turn = 0; turn < kTurnsFwd; ++turn) {
+  for (int turn = 0; turn < turns; ++turn) {
 #pragma unroll
     for (int j = 0; j < kTaps; ++j) {
       const int n = turn * kTaps + j;   // input rows staged before this one
@@ -75,7 +94,7 @@ __global__ void __launch_bounds__(kWave) k_ssim_fwd(const T* __restrict__ X, con
         sx[q][kWave + lane] = xb;
         sy[q][kWave + lane] = yb;
       }
-      if (n + 1 < kTaps * kTurnsFwd) fetch(ir + 1);
+      if (n + 1 < kTaps * turns) fetch(ir + 1);
       __syncthreads();
       T a = 0, b = 0, aa = 0, bb = 0, ab = 0, xc = 0, yc = 0;
 #pragma unroll
@@ -87,7 +106,7 @@ __global__ void __launch_bounds__(kWave) k_ssim_fwd(const T* __restrict__ X, con
       }
       ring[j][0] = a; ring[j][1] = b; ring[j][2] = aa; ring[j][3] = bb; ring[j][4] = ab;
       // this input row is an output row of the wave: its L1 term
-      if (n >= kHalo && n < kHalo + kRowsFwd && ir < H && inc) l1 += (double)(xc > yc ? xc - yc : yc - xc);
+      if (n >= kHalo && n < kHalo + rows && ir < H && inc) l1 += (double)(xc > yc ? xc - yc : yc - xc);
       if (n >= 2 * kHalo) {
         // ring slot (j + 1 + t) mod 11 holds input row ir - 10 + t
         T mx = 0, my = 0, mxx = 0, myy = 0, mxy = 0;
@@ -132,7 +151,7 @@ __global__ void __launch_bounds__(kWave) k_ssim_fwd(const T* __restrict__ X, con
 template <typename T>
 __global__ void __launch_bounds__(kWave) k_ssim_bwd(const T* __restrict__ X, const T* __restrict__ Y,
                                                     const T* __restrict__ dmaps, int32_t H, int32_t W, Win<T> win,
-                                                    T scale, T* __restrict__ dx_out) {
+                                                    int turns, T scale, T* __restrict__ dx_out) {
   __shared__ T sd[2][3][kSpan];
   const int lane = threadIdx.x;
   const int64_t plane = blockIdx.z;
@@ -141,7 +160,7 @@ __global__ void __launch_bounds__(kWave) k_ssim_bwd(const T* __restrict__ X, con
   const int c = blockIdx.x * kWave + lane;
   const int ca = c - kHalo, cb = c + kWave - kHalo;
   const bool ina = ca >= 0 && ca < W, inb = lane < 2 * kHalo && cb < W, inc = c < W;
-  const int r0 = blockIdx.y * kRowsBwd;
+  const int r0 = blockIdx.y * rows_of(turns);
   T da[3], db[3], xo, yo;   // the next input row of the maps; x, y of the next output row
   auto fetch = [&](int ir) {
     const bool rin = ir >= 0 && ir < H;
@@ -158,7 +177,7 @@ __global__ void __launch_bounds__(kWave) k_ssim_bwd(const T* __restrict__ X, con
   };
   fetch(r0 - kHalo);
   T ring[kTaps][3];
-  for (int turn = 0; turn < kTurnsBwd; ++turn) {
+  for (int turn = 0; turn < turns; ++turn) {
 #pragma unroll
     for (int j = 0; j < kTaps; ++j) {
       const int n = turn * kTaps + j;
@@ -170,7 +189,7 @@ __global__ void __launch_bounds__(kWave) k_ssim_bwd(const T* __restrict__ X, con
         if (lane < 2 * kHalo) sd[q][m][kWave + lane] = db[m];
       }
       const T xv = xo, yv = yo;
-      if (n + 1 < kTaps * kTurnsBwd) fetch(ir + 1);
+      if (n + 1 < kTaps * turns) fetch(ir + 1);
       __syncthreads();
       T a = 0, b = 0, e = 0;
 #pragma unroll
@@ -229,7 +248,8 @@ using namespace tide;
 extern "C" size_t tide_loss_ws_bytes(int32_t n_views, int32_t height, int32_t width, int32_t dtype) {
   const size_t es = dtype == TIDE_F64 ? 8 : 4;
   const size_t planes = (size_t)n_views * 3;
-  const size_t nblk = planes * ceil_div(width, kWave) * ceil_div(height, kRowsFwd);
+  const int rows = rows_of(Turns(n_views, height, width, dtype).fwd);
+  const size_t nblk = planes * ceil_div(width, kWave) * ceil_div(height, rows);
   return align_up(3 * planes * (size_t)height * width * es) + align_up(2 * nblk * sizeof(double)) + 256;
 }
 
@@ -246,8 +266,10 @@ extern "C" tide_status tide_loss(const void* image, const void* target, int32_t 
     return TIDE_ECAPACITY;
   }
   hipStream_t st = (hipStream_t)stream;
-  const dim3 grid((uint32_t)ceil_div(width, kWave), (uint32_t)ceil_div(height, kRowsFwd), (uint32_t)(n_views * 3));
-  const dim3 gridb((uint32_t)ceil_div(width, kWave), (uint32_t)ceil_div(height, kRowsBwd), (uint32_t)(n_views * 3));
+  const Turns turns(n_views, height, width, dtype);
+  const uint32_t strips = (uint32_t)ceil_div(width, kWave), planes = (uint32_t)(n_views * 3);
+  const dim3 grid(strips, (uint32_t)ceil_div(height, rows_of(turns.fwd)), planes);
+  const dim3 gridb(strips, (uint32_t)ceil_div(height, rows_of(turns.bwd)), planes);
   const int64_t nblk = (int64_t)grid.x * grid.y * grid.z;
   const double n_all = 3.0 * height * width * n_views;
   Carver cv(ws);
@@ -256,18 +278,18 @@ extern "C" tide_status tide_loss(const void* image, const void* target, int32_t 
     double* part = cv.take<double>(2 * nblk);
     const Win<float> w = make_window<float>();
     TIDE_TIMED("loss_fwd", st, hipLaunchKernelGGL(k_ssim_fwd<float>, grid, dim3(kWave), 0, st, (const float*)image, (const float*)target, height,
-                       width, w, dm, part));
+                       width, w, turns.fwd, dm, part));
     TIDE_TIMED("loss_bwd", st, hipLaunchKernelGGL(k_ssim_bwd<float>, gridb, dim3(kWave), 0, st, (const float*)image, (const float*)target, dm,
-                       height, width, w, (float)(1.0 / n_all), (float*)d_dimage));
+                       height, width, w, turns.bwd, (float)(1.0 / n_all), (float*)d_dimage));
     hipLaunchKernelGGL(k_loss_final, dim3(1), dim3(1024), 0, st, part, nblk, 1.0 / n_all, d_loss);
   } else {
     double* dm = cv.take<double>(3 * (size_t)n_views * 3 * height * width);
     double* part = cv.take<double>(2 * nblk);
     const Win<double> w = make_window<double>();
     TIDE_TIMED("loss_fwd", st, hipLaunchKernelGGL(k_ssim_fwd<double>, grid, dim3(kWave), 0, st, (const double*)image, (const double*)target,
-                       height, width, w, dm, part));
+                       height, width, w, turns.fwd, dm, part));
     TIDE_TIMED("loss_bwd", st, hipLaunchKernelGGL(k_ssim_bwd<double>, gridb, dim3(kWave), 0, st, (const double*)image, (const double*)target, dm,
-                       height, width, w, 1.0 / n_all, (double*)d_dimage));
+                       height, width, w, turns.bwd, 1.0 / n_all, (double*)d_dimage));
     hipLaunchKernelGGL(k_loss_final, dim3(1), dim3(1024), 0, st, part, nblk, 1.0 / n_all, d_loss);
   }
   TIDE_LAUNCH_CHECK("tide_loss");
