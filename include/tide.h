@@ -324,6 +324,22 @@ tide_status tide_render_bwd_adam(tide_pool* pool, const tide_camera* cams, int32
                                  int64_t n_blocks, void* ws, size_t ws_bytes, void* stream);
 
 /* ------------------------------------------------------------------------
+ * Row-major tables to and from the layouts above (the differentiable render
+ * of a dense (N, 59) table).
+ * tide_rows_to_blocks: row i of theta [n][59] goes to slot i / block_rows, row
+ * i % block_rows of params; the other rows of the n_slots slots become 0.
+ * Block k sits in slot k: slot_block, slot_rows [n_slots] and the first
+ * max(1, ceil(n / block_rows)) entries of order are written to say so.
+ * tide_dense_grad: out [n][59], row i = active[i] ? column act_idx[i] of grad
+ * : 0, for n <= proj->n_pidx rows (a pool whose pidx is the row).
+ * ---------------------------------------------------------------------- */
+tide_status tide_rows_to_blocks(const void* theta, int64_t n, int32_t block_rows, int32_t n_slots,
+                                int32_t dtype, void* params, int32_t* slot_block,
+                                int32_t* slot_rows, int32_t* order, void* stream);
+tide_status tide_dense_grad(const tide_proj* proj, const void* grad, int64_t grad_ld, int64_t n,
+                            void* out, void* stream);
+
+/* ------------------------------------------------------------------------
  * Out-of-core block tier (Sec. 3.3 to 3.5; Alg. 1).  A host object owns the
  * SSD log store (an immutable base segment plus append-only patch segments
  * and Index[k] = (file_id, offset, size, version), Sec. 3.4), a host LRU

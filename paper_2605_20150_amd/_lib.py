@@ -128,6 +128,8 @@ SIGNATURES = {
     "tide_render_bwd_adam": (C.c_int32, [_P(tide_pool), _P(tide_camera), C.c_int32, _P(tide_proj), _P(tide_bins),
                                          _P(tide_frame), _P(C.c_float), _vp, _P(tide_adam_cfg), _vp, _vp, C.c_int64,
                                          _vp, C.c_size_t, _vp]),
+    "tide_rows_to_blocks": (C.c_int32, [_vp, C.c_int64, C.c_int32, C.c_int32, C.c_int32, _vp, _vp, _vp, _vp, _vp]),
+    "tide_dense_grad": (C.c_int32, [_P(tide_proj), _vp, C.c_int64, C.c_int64, _vp, _vp]),
     "tide_timer_arm": (C.c_int32, [C.c_char_p, _vp, _vp]),
     "tide_residency_create": (C.c_int32, [_P(tide_store_cfg), _P(tide_pool), _vp, _vp, _P(_vp)]),
     "tide_residency_destroy": (C.c_int32, [_vp]),

@@ -15,6 +15,7 @@ from dataclasses import dataclass
 
 import numpy as np
 import torch
+from torch.autograd import forward_ad
 
 from . import _lib as L
 
@@ -32,6 +33,16 @@ def _dtype_code(dt: torch.dtype) -> int:
     if dt == torch.float64:
         return L.TIDE_F64
     raise TypeError(f"unsupported dtype {dt}")
+
+
+def _plain(t: torch.Tensor) -> bool:
+    """A tensor of values on the current GPU that a kernel may read in torch's
+    place: float32 or float64, nothing recorded, traced, batched or carrying a
+    tangent."""
+    return (type(t) in (torch.Tensor, torch.nn.Parameter) and t.is_cuda
+            and t.device.index == torch.cuda.current_device() and t.dtype in (torch.float32, torch.float64)
+            and not t.requires_grad and not torch._C._functorch.is_functorch_wrapped_tensor(t)
+            and forward_ad._current_level < 0 and not torch.compiler.is_compiling())
 
 
 class Buffers:
@@ -83,9 +94,27 @@ class Pool:
     def from_dense(cls, theta: torch.Tensor, block_rows: int = 65536, extra_slots: int = 0):
         """All-resident pool holding rows of ``theta`` (N, 59) in blocks of
         ``block_rows``; block k sits in slot k."""
+        return cls._from_dense(theta, block_rows, extra_slots, torch.zeros)
+
+    @classmethod
+    def _from_dense(cls, theta, block_rows, extra_slots, state):
+        """``state`` (torch.zeros or torch.empty) makes the moments and steps."""
         N = theta.shape[0]
         K = max(1, math.ceil(N / block_rows))
         dev = theta.device
+        if (theta.dim() == 2 and theta.shape[1] == D and 0 < N and 0 <= extra_slots and 0 < block_rows
+                and _plain(theta) and theta.is_contiguous()):
+            # one launch in place of fills, copies and a transpose, and no wait for
+            # the slot tables' way from host memory
+            S = K + int(extra_slots)
+            params = torch.empty((S, D, block_rows), dtype=theta.dtype, device=dev)
+            sb, rows, order = (torch.empty((k,), dtype=torch.int32, device=dev) for k in (S, S, K))
+            L.check(L.load().tide_rows_to_blocks(C.c_void_p(theta.data_ptr()), N, block_rows, S,
+                                                 _dtype_code(theta.dtype), C.c_void_p(params.data_ptr()),
+                                                 C.c_void_p(sb.data_ptr()), C.c_void_p(rows.data_ptr()),
+                                                 C.c_void_p(order.data_ptr()), C.c_void_p(_stream())))
+            return cls(params, *(state(params.shape, dtype=theta.dtype, device=dev) for _ in range(2)),
+                       state((S, block_rows), dtype=torch.int32, device=dev), sb, rows, order)
         pad = torch.zeros((K * block_rows, D), dtype=theta.dtype, device=dev)
         pad[:N] = theta
         params = pad.view(K, block_rows, D).transpose(1, 2).contiguous()
@@ -227,7 +256,10 @@ class Rasterizer:
     def bin_sort(self, proj: Proj, tiles_x: int, tiles_y: int) -> L.tide_bins:
         V, N = proj.n_cams, proj.n_pidx
         if self.inst_cap == 0:
-            self.inst_cap = max(4 * V * N, 1 << 16)
+            # up to a million (25 MB of workspace) at once what small scenes can
+            # emit at most: a second binning for want of room costs more (0.1 to
+            # 0.3 ms) than the room
+            self.inst_cap = max(4 * V * N, 1 << 16, min(V * N * tiles_x * tiles_y, 1 << 20))
         bins = L.tide_bins()
         pc = proj.c()
         for _ in range(4):
@@ -334,6 +366,15 @@ class Rasterizer:
 def dense_grad(proj: Proj, grad: torch.Tensor, n: int) -> torch.Tensor:
     """Compact [59][n_active] gradient -> dense (n, 59) for an all-resident
     pool whose pidx equals the global row id."""
+    if (0 < n <= proj.n_pidx <= grad.shape[-1] and _plain(grad) and grad.dim() == 2 and grad.shape[0] == D
+            and grad.stride(1) == 1 and grad.stride(0) >= grad.shape[1] and _dtype_code(grad.dtype) == proj.dtype
+            and proj.active.shape[0] == proj.n_pidx):
+        # one launch, and the host does not wait for the active rows' number
+        out = torch.empty((n, D), dtype=grad.dtype, device=grad.device)
+        pc = proj.c()
+        L.check(L.load().tide_dense_grad(C.byref(pc), C.c_void_p(grad.data_ptr()), grad.stride(0), n,
+                                         C.c_void_p(out.data_ptr()), C.c_void_p(_stream())))
+        return out
     act = proj.active[:n].bool()
     idx = proj.act_idx[:n][act].long()
     out = torch.zeros((n, D), dtype=grad.dtype, device=grad.device)
@@ -346,7 +387,8 @@ class TideRasterize(torch.autograd.Function):
 
     @staticmethod
     def forward(ctx, theta, cams, bg, block_rows, rast):
-        pool = Pool.from_dense(theta.detach().contiguous(), block_rows)
+        # neither direction reads the moments and steps
+        pool = Pool._from_dense(theta.detach().contiguous(), block_rows, 0, torch.empty)
         proj, bins, fr = rast.forward(pool, cams, bg)
         ctx.save = (pool, cams, proj, bins, fr, bg, rast, theta.shape[0])
         return fr.image
