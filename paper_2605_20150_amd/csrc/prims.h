@@ -154,17 +154,56 @@ __device__ inline void write_tail(const ScanTail& tail, unsigned long long t, in
   for (int k = 0; k < tail.copy_n; ++k) tail.copy_dst[k] = tail.copy_src[k];
 }
 
-// kSums: partial holds the blocks' sums (not yet scanned); each block adds
-// up its predecessors' itself and block 0 writes the total (one launch
-// fewer; used when there are at most 1024 blocks).
-template <typename In, bool kSums, typename Out, bool kVec>
+// Where a block of the down-sweep gets the sum of the blocks before it from.
+//   kScanned  partial holds the scan of the blocks' sums;
+//   kSums     partial holds the blocks' sums, and each block adds up its
+//             predecessors' itself (one launch fewer; at most 1024 blocks);
+//   kSelf     no sums: each block reads its predecessors' elements itself, for
+//             at most kScanSelfBlocks blocks.  A launch fewer; the elements must
+//             not be written over by the scan.  Five blocks (reduce + down -> one
+//             kernel, us): active rows 2.6 + 3.6 -> 3.1, instance offsets 4.6 +
+//             6.1 -> 7.3, visible pairs 3.0 + 5.9 -> 8.3.  A predecessor adds
+//             four 16-byte loads per thread; past eight the launch is cheaper.
+// The first block writes the total (kSelf: the last one).
+enum ScanFrom { kScanned, kSums, kSelf };
+constexpr int64_t kScanSelfBlocks = 8;
+
+// The sum of the elements of the blocks before this one, given to every thread
+// (wt: one word per wave; synchronises).
+template <bool kVec, typename In>
+__device__ inline unsigned long long sum_self(const In& in, int64_t n, unsigned long long* wt) {
+  const int64_t mine = (int64_t)blockIdx.x * kScanTile, lim = mine < n ? mine : n;
+  unsigned long long s = 0;
+  int64_t j = 4 * threadIdx.x;
+#pragma unroll 4
+  for (; j + 4 <= lim; j += 4 * kScanThreads) {
+    uint32_t v[4];
+    if (kVec) {
+      in.load4(j, v);
+    } else {
+#pragma unroll
+      for (int k = 0; k < 4; ++k) v[k] = in(j + k);
+    }
+    s += (unsigned long long)v[0] + v[1] + v[2] + v[3];
+  }
+  for (; j < lim; ++j) s += in(j);   // one thread's last group, where n cuts it
+  s = wave_sum(s);
+  if (__lane_id() == 0) wt[threadIdx.x / kWave] = s;
+  __syncthreads();
+  unsigned long long t = 0;
+#pragma unroll
+  for (int q = 0; q < kScanThreads / kWave; ++q) t += wt[q];
+  return t;
+}
+
+template <typename In, ScanFrom kFrom, typename Out, bool kVec>
 __global__ void __launch_bounds__(kScanThreads) k_scan_down(In in, int64_t n_max, const unsigned long long* d_n,
                                                             const unsigned long long* partial,
                                                             Out out, int64_t nb,
                                                             unsigned long long* total, ScanTail tail) {
   const int64_t n = dev_count(n_max, d_n);
   __shared__ unsigned long long bpre[kScanThreads / kWave + 1];
-  if (kSums) {
+  if (kFrom == kSums) {
     // predecessors' sums (and, in block 0, all the sums for the total)
     const int64_t upto = blockIdx.x == 0 ? nb : (int64_t)blockIdx.x;
     unsigned long long a = 0;
@@ -189,6 +228,11 @@ __global__ void __launch_bounds__(kScanThreads) k_scan_down(In in, int64_t n_max
   uint32_t s = 0;
 #pragma unroll
   for (int k = 0; k < kScanItems; ++k) s += v[k];
+  unsigned long long bp;
+  if (kFrom == kSelf)
+    bp = sum_self<kVec>(in, n, bpre);
+  else
+    bp = kFrom == kSums ? bpre[kScanThreads / kWave] : partial[blockIdx.x];
   // exclusive scan of the 256 thread sums
   const uint32_t inc = wave_incl_scan(s);
   __shared__ uint32_t wtot[kScanThreads / kWave];
@@ -197,8 +241,13 @@ __global__ void __launch_bounds__(kScanThreads) k_scan_down(In in, int64_t n_max
   __syncthreads();
   uint32_t wpre = 0;
   for (int q = 0; q < w; ++q) wpre += wtot[q];
-  const unsigned long long bp = kSums ? bpre[kScanThreads / kWave] : partial[blockIdx.x];
   uint32_t run = (uint32_t)bp + wpre + inc - s;
+  if (kFrom == kSelf && blockIdx.x == nb - 1 && threadIdx.x == 0) {
+    unsigned long long t = bp;
+    for (int q = 0; q < kScanThreads / kWave; ++q) t += wtot[q];
+    *total = t;
+    write_tail(tail, t, n);
+  }
   if (kVec && base + kScanItems <= n) {
     uint32_t o[kScanItems];
 #pragma unroll
@@ -219,40 +268,36 @@ __global__ void __launch_bounds__(kScanThreads) k_scan_down(In in, int64_t n_max
 
 // Exclusive scan of in(0..n) into the sink out; total (u64, device)
 // receives the sum, and the tail its extras.  partial needs
-// ceil(n_max/4096) u64 entries; d_n as for dev_count.
+// ceil(n_max/4096) u64 entries; d_n as for dev_count.  in_place: the sink
+// writes over the elements.
 template <typename In, typename Out>
 inline void scan_to(In in, int64_t n, Out out, unsigned long long* partial, unsigned long long* total,
-                    hipStream_t st, const unsigned long long* d_n = nullptr, ScanTail tail = ScanTail{}) {
+                    hipStream_t st, const unsigned long long* d_n, ScanTail tail, bool in_place) {
   const int64_t nb = ceil_div(n > 0 ? n : 1, kScanTile);
   const bool vec = in.aligned() && out.aligned();
-  if (vec)
-    hipLaunchKernelGGL((k_scan_reduce<In, true>), dim3((uint32_t)nb), dim3(kScanThreads), 0, st, in, n, d_n, partial);
-  else
-    hipLaunchKernelGGL((k_scan_reduce<In, false>), dim3((uint32_t)nb), dim3(kScanThreads), 0, st, in, n, d_n, partial);
+  const dim3 grid((uint32_t)nb), block(kScanThreads);
+  if (nb <= kScanSelfBlocks && !in_place) {
+    auto down = vec ? k_scan_down<In, kSelf, Out, true> : k_scan_down<In, kSelf, Out, false>;
+    hipLaunchKernelGGL(down, grid, block, 0, st, in, n, d_n, (const unsigned long long*)partial, out, nb, total, tail);
+    return;
+  }
+  auto reduce = vec ? k_scan_reduce<In, true> : k_scan_reduce<In, false>;
+  hipLaunchKernelGGL(reduce, grid, block, 0, st, in, n, d_n, partial);
   if (nb <= 1024) {
-    if (vec)
-      hipLaunchKernelGGL((k_scan_down<In, true, Out, true>), dim3((uint32_t)nb), dim3(kScanThreads), 0, st, in, n, d_n,
-                         (const unsigned long long*)partial, out, nb, total, tail);
-    else
-      hipLaunchKernelGGL((k_scan_down<In, true, Out, false>), dim3((uint32_t)nb), dim3(kScanThreads), 0, st, in, n,
-                         d_n, (const unsigned long long*)partial, out, nb, total, tail);
+    auto down = vec ? k_scan_down<In, kSums, Out, true> : k_scan_down<In, kSums, Out, false>;
+    hipLaunchKernelGGL(down, grid, block, 0, st, in, n, d_n, (const unsigned long long*)partial, out, nb, total, tail);
     return;
   }
   hipLaunchKernelGGL(k_scan_partials, dim3(1), dim3(1024), 0, st, partial, nb, total, tail, n, d_n);
-  if (vec)
-    hipLaunchKernelGGL((k_scan_down<In, false, Out, true>), dim3((uint32_t)nb), dim3(kScanThreads), 0, st, in, n, d_n,
-                       (const unsigned long long*)partial, out, nb, total, tail);
-  else
-    hipLaunchKernelGGL((k_scan_down<In, false, Out, false>), dim3((uint32_t)nb), dim3(kScanThreads), 0, st, in, n,
-                       d_n, (const unsigned long long*)partial, out, nb, total, tail);
+  auto down = vec ? k_scan_down<In, kScanned, Out, true> : k_scan_down<In, kScanned, Out, false>;
+  hipLaunchKernelGGL(down, grid, block, 0, st, in, n, d_n, (const unsigned long long*)partial, out, nb, total, tail);
 }
 
-// Exclusive scan into an offsets array.
-template <typename In>
-inline void scan_exclusive(In in, int64_t n, uint32_t* out, unsigned long long* partial,
+// Exclusive scan into an offsets array (which may be the elements' own).
+inline void scan_exclusive(ArrayIn in, int64_t n, uint32_t* out, unsigned long long* partial,
                            unsigned long long* total, hipStream_t st, const unsigned long long* d_n = nullptr,
                            ScanTail tail = ScanTail{}) {
-  scan_to(in, n, OffsetsOut{out}, partial, total, st, d_n, tail);
+  scan_to(in, n, OffsetsOut{out}, partial, total, st, d_n, tail, in.a == out);
 }
 
 inline size_t scan_partial_count(int64_t n) { return (size_t)ceil_div(n > 0 ? n : 1, kScanTile); }
@@ -297,7 +342,7 @@ template <int R, int W = kSortWaves>
 struct TileLds {
   uint32_t wcnt[W][256];
   uint32_t gbase[256], lstart[256], wsum[4];
-  uint32_t skey[kWave * W * R], sval[kWave * W * R];
+  alignas(16) uint32_t skey[kWave * W * R], sval[kWave * W * R];
 };
 
 // Ranks the keys of tile [b0, b0 + 64 W R) ∩ [0, n) by digit (key >> shift)
