@@ -26,7 +26,6 @@ typedef float f32x2 __attribute__((ext_vector_type(2)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int kBK = 32;
-constexpr int kLdk = kBK + 8;   // LDS row stride in bf16 (80 bytes, 16-byte aligned rows)
 
 // Nearest bfloat16 (ties to even) of an FP32 value, as its 16-bit pattern.
 __device__ inline uint16_t bf16_bits(float f) {
@@ -159,18 +158,23 @@ __global__ __launch_bounds__(256) void k_gemm_direct(const float* __restrict__ A
 //   kE_MASK       C = mask[m][n] > 0 ? acc : 0   (ReLU adjoint)
 //   kE_STORE      C = acc
 // T x T outputs per 256-thread workgroup (four waves in
-// a square, (T/2)^2 each), K staged 32 at a time through LDS as bf16 rows
-// [row][k], so that one 16-byte LDS read gives a lane its eight operands.
+// a square, (T/2)^2 each), K staged KB (32 or 64) at a time through LDS as bf16
+// rows [row][k], so that one 16-byte LDS read gives a lane its eight operands.
 // Eight consecutive k of one row are a thread's staging unit: loaded (from
 // an operand that is contiguous along the other index as eight coalesced
 // loads, one per k, so the transposition costs nothing), rounded in
 // registers and written with one conflict-free 16-byte LDS store.  The next
-// K step's loads are in flight while the matrix cores work on this one.
-// T = 128 holds 64 accumulators per lane and reads each operand half as
-// often as T = 64, which is for the products too small to fill the chip.
-// 256 x 512 -> 65536: forward 66 us (115 us with 64 x 64 tiles, integer
-// rounding and no loads in flight), weight gradient 156 us (335 us, of which
-// 62 us the bias gradient as a kernel of its own).
+// K step's loads are in flight while the matrix cores work on this one, none
+// of them behind a bounds check of its own: rows and k past the edges are read
+// from inside and made zeros in the last step only.  T = 128 holds 64
+// accumulators per lane and reads each operand half as often as T = 64; T = 32
+// is for the products too small to fill the chip, where the staging of a
+// workgroup is what it waits for.
+// 256 x 512 -> 65536: forward 65 us (115 us with 64 x 64 tiles, integer
+// rounding and no loads in flight), weight gradient 88 us (335 us, of which
+// 62 us the bias gradient as a kernel of its own; 149 us with checked loads).
+// Weight gradient 256 x 512 -> 512: 7.4 us (18.7 us with 64 x 64 tiles and
+// checked loads, 11.8 us with the tiles alone).
 //
 // Grid: workgroup ids walk the MAJOR dimension eight at a time, so that the
 // workgroups that share its operand tile run on one XCD and meet in its L2.
@@ -183,7 +187,7 @@ __global__ __launch_bounds__(256) void k_gemm_direct(const float* __restrict__ A
 // operand (K for kA_KC / kB_WKC, M for kA_MC, N for kB_WNC / kB_FNC) and
 // every leading dimension are multiples of 8, and base pointers are 16-byte
 // aligned.
-template <int T, int AK, int BK, int EPI, int MAJOR>
+template <int T, int KB, int AK, int BK, int EPI, int MAJOR>
 __global__ __launch_bounds__(256) void k_gemm(const float* __restrict__ A, int64_t lda, const void* __restrict__ Bv,
                                               int64_t ldb, float* __restrict__ C, int64_t ldc,
                                               const float* __restrict__ bias, const float* __restrict__ mask,
@@ -192,12 +196,14 @@ __global__ __launch_bounds__(256) void k_gemm(const float* __restrict__ A, int64
   constexpr bool kSplitB = BK == kB_FNC;
   constexpr bool kSumA = AK == kA_MC && EPI == kE_STORE;
   constexpr int WT = T / 32;             // 16 x 16 tiles per wave and side
-  constexpr int UN = T * kBK / 8 / 256;  // staging units per thread and operand (1 or 2)
-  __shared__ __attribute__((aligned(16))) uint16_t sAh[T][kLdk];
-  __shared__ __attribute__((aligned(16))) uint16_t sAl[T][kLdk];
-  __shared__ __attribute__((aligned(16))) uint16_t sBh[T][kLdk];
-  __shared__ __attribute__((aligned(16))) uint16_t sBl[kSplitB ? T : 1][kLdk];
-  __shared__ float sF[kSumA ? kBK : 1][kSumA ? T : 1];
+  constexpr int UN = T * KB / 8 / 256;   // staging units per thread and operand
+  constexpr int LD = KB + 8;             // LDS row stride in bf16 (16-byte aligned rows, 4 banks apart)
+  static_assert(KB == kBK || (AK == kA_MC && BK == kB_FNC), "deeper stages: operands that are not contiguous along k");
+  __shared__ __attribute__((aligned(16))) uint16_t sAh[T][LD];
+  __shared__ __attribute__((aligned(16))) uint16_t sAl[T][LD];
+  __shared__ __attribute__((aligned(16))) uint16_t sBh[T][LD];
+  __shared__ __attribute__((aligned(16))) uint16_t sBl[kSplitB ? T : 1][LD];
+  __shared__ float sF[kSumA ? KB : 1][kSumA ? T : 1];
 
   // id = (major / 8) * 8 * minor-count + minor * 8 + major % 8
   const int n_minor = MAJOR == kMajN ? tm : tn, n_major = MAJOR == kMajN ? tn : tm;
@@ -238,34 +244,52 @@ __global__ __launch_bounds__(256) void k_gemm(const float* __restrict__ A, int64
   float dsum = 0.f;
   const bool want_db = kSumA && n0 == 0;
 
-  auto fetch = [&](int k0) {
+  // Every load is issued whatever the edges (a guarded one costs its own branch
+  // or waits): rows past M or N read the last one (their outputs are not
+  // stored), k past K the last chunk or k, whose values become zeros.
+  const float* pa[UN];
+  const float* px[kSplitB ? UN : 1];
+  const uint16_t* pw[BK == kB_WKC ? UN : 1];
+#pragma unroll
+  for (int u = 0; u < UN; ++u) {
+    const int m = m0 + a_row[u] < M ? m0 + a_row[u] : M - 1, n = n0 + b_row[u] < N ? n0 + b_row[u] : N - 1;
+    pa[u] = AK == kA_KC ? A + (int64_t)m * lda : A + m;
+    if (BK == kB_WKC) pw[BK == kB_WKC ? u : 0] = static_cast<const uint16_t*>(Bv) + (int64_t)n * ldb;
+    if (BK == kB_FNC) px[kSplitB ? u : 0] = static_cast<const float*>(Bv) + n;
+  }
+  // eight values of one row or column from k on; tail: k may pass K
+  auto along_k = [&](const float* p, int k, bool tail, float (&v)[8]) {   // K and k are multiples of 8
+    const bool in = !tail || k < K;
+    const float4* q = reinterpret_cast<const float4*>(p + (in ? k : K - 8));
+    const float4 x = q[0], y = q[1];
+    v[0] = in ? x.x : 0.f; v[1] = in ? x.y : 0.f; v[2] = in ? x.z : 0.f; v[3] = in ? x.w : 0.f;
+    v[4] = in ? y.x : 0.f; v[5] = in ? y.y : 0.f; v[6] = in ? y.z : 0.f; v[7] = in ? y.w : 0.f;
+  };
+  auto across_k = [&](const float* p, int64_t ld, int k, bool tail, float (&v)[8]) {
+#pragma unroll
+    for (int j = 0; j < 8; ++j) v[j] = p[(int64_t)(!tail || k + j < K ? k + j : K - 1) * ld];
+    if (tail) {
+#pragma unroll
+      for (int j = 0; j < 8; ++j) v[j] = k + j < K ? v[j] : 0.f;
+    }
+  };
+  auto fetch_from = [&](int k0, bool tail) {
 #pragma unroll
     for (int u = 0; u < UN; ++u) {
-      const int m = m0 + a_row[u], k = k0 + a_k[u];
-      if (AK == kA_KC) {
-        float4 x = make_float4(0.f, 0.f, 0.f, 0.f), y = x;
-        if (m < M && k < K) {
-          const float4* p = reinterpret_cast<const float4*>(A + (int64_t)m * lda + k);
-          x = p[0];
-          y = p[1];
-        }
-        av[u][0] = x.x; av[u][1] = x.y; av[u][2] = x.z; av[u][3] = x.w;
-        av[u][4] = y.x; av[u][5] = y.y; av[u][6] = y.z; av[u][7] = y.w;
-      } else {
-#pragma unroll
-        for (int j = 0; j < 8; ++j) av[u][j] = m < M && k + j < K ? A[(int64_t)(k + j) * lda + m] : 0.f;
+      if (AK == kA_KC)
+        along_k(pa[u], k0 + a_k[u], tail, av[u]);
+      else
+        across_k(pa[u], lda, k0 + a_k[u], tail, av[u]);
+      const int k = k0 + b_k[u];
+      if (BK == kB_WKC) {
+        const bool in = !tail || k < K;
+        const uint4 x = *reinterpret_cast<const uint4*>(pw[BK == kB_WKC ? u : 0] + (in ? k : K - 8));
+        bw[BK == kB_WKC ? u : 0] = make_uint4(in ? x.x : 0u, in ? x.y : 0u, in ? x.z : 0u, in ? x.w : 0u);
+      } else if (BK == kB_FNC) {
+        across_k(px[kSplitB ? u : 0], ldb, k, tail, bf[kSplitB ? u : 0]);
       }
     }
-    if (BK == kB_WKC) {
-      const uint16_t* W = static_cast<const uint16_t*>(Bv);
-#pragma unroll
-      for (int u = 0; u < UN; ++u) {
-        const int n = n0 + b_row[u], k = k0 + b_k[u];
-        bw[BK == kB_WKC ? u : 0] = make_uint4(0u, 0u, 0u, 0u);
-        if (n < N && k < K)
-          bw[BK == kB_WKC ? u : 0] = *reinterpret_cast<const uint4*>(W + (int64_t)n * ldb + k);
-      }
-    } else if (BK == kB_WNC) {
+    if (BK == kB_WNC) {
       const uint16_t* W = static_cast<const uint16_t*>(Bv);
       const int n = n0 + p_row, k = k0 + p_k;
 #pragma unroll
@@ -273,16 +297,13 @@ __global__ __launch_bounds__(256) void k_gemm(const float* __restrict__ A, int64
         bp[BK == kB_WNC ? j : 0] = p_on && n < N && k + j < K
                        ? *reinterpret_cast<const uint32_t*>(W + (int64_t)(k + j) * ldb + n)
                        : 0u;
-    } else {
-      const float* X = static_cast<const float*>(Bv);
-#pragma unroll
-      for (int u = 0; u < UN; ++u) {
-        const int n = n0 + b_row[u], k = k0 + b_k[u];
-#pragma unroll
-        for (int j = 0; j < 8; ++j)
-          bf[kSplitB ? u : 0][j] = n < N && k + j < K ? X[(int64_t)(k + j) * ldb + n] : 0.f;
-      }
     }
+  };
+  auto fetch = [&](int k0) {
+    if (k0 + KB <= K)
+      fetch_from(k0, false);
+    else
+      fetch_from(k0, true);
   };
   auto stage = [&]() {
 #pragma unroll
@@ -324,32 +345,36 @@ __global__ __launch_bounds__(256) void k_gemm(const float* __restrict__ A, int64
   };
 
   fetch(0);
-  for (int k0 = 0; k0 < K; k0 += kBK) {
+  for (int k0 = 0; k0 < K; k0 += KB) {
     stage();
     __syncthreads();
-    if (k0 + kBK < K) fetch(k0 + kBK);
+    if (k0 + KB < K) fetch(k0 + KB);
     if (want_db && t < T) {
 #pragma unroll 8
-      for (int j = 0; j < kBK; ++j) dsum += sF[kSumA ? j : 0][kSumA ? t : 0];   // rows past K hold zeros
+      for (int j = 0; j < KB; ++j) dsum += sF[kSumA ? j : 0][kSumA ? t : 0];   // rows past K hold zeros
     }
-    // matrix cores: lane holds row (lane % 16), k = 8 (lane / 16) .. +7
-    const int r = lane & 15, kc = (lane >> 4) * 8;
-    bf16x8 bh[WT], bl[kSplitB ? WT : 1];
+    // matrix cores: lane holds row (lane % 16), k = 8 (lane / 16) .. +7 of a chunk of 32
 #pragma unroll
-    for (int j = 0; j < WT; ++j) {
-      bh[j] = *reinterpret_cast<const bf16x8*>(&sBh[wn + 16 * j + r][kc]);
-      if (kSplitB) bl[kSplitB ? j : 0] = *reinterpret_cast<const bf16x8*>(&sBl[kSplitB ? wn + 16 * j + r : 0][kc]);
-    }
-#pragma unroll
-    for (int i = 0; i < WT; ++i) {
-      const bf16x8 ah = *reinterpret_cast<const bf16x8*>(&sAh[wm + 16 * i + r][kc]);
-      const bf16x8 al = *reinterpret_cast<const bf16x8*>(&sAl[wm + 16 * i + r][kc]);
+    for (int c = 0; c < KB; c += kBK) {
+      if (k0 + c >= K) break;
+      const int r = lane & 15, kc = c + (lane >> 4) * 8;
+      bf16x8 bh[WT], bl[kSplitB ? WT : 1];
 #pragma unroll
       for (int j = 0; j < WT; ++j) {
-        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ah, bh[j], acc[i][j], 0, 0, 0);
-        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(al, bh[j], acc[i][j], 0, 0, 0);
-        if (kSplitB)
-          acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ah, bl[kSplitB ? j : 0], acc[i][j], 0, 0, 0);
+        bh[j] = *reinterpret_cast<const bf16x8*>(&sBh[wn + 16 * j + r][kc]);
+        if (kSplitB) bl[kSplitB ? j : 0] = *reinterpret_cast<const bf16x8*>(&sBl[kSplitB ? wn + 16 * j + r : 0][kc]);
+      }
+#pragma unroll
+      for (int i = 0; i < WT; ++i) {
+        const bf16x8 ah = *reinterpret_cast<const bf16x8*>(&sAh[wm + 16 * i + r][kc]);
+        const bf16x8 al = *reinterpret_cast<const bf16x8*>(&sAl[wm + 16 * i + r][kc]);
+#pragma unroll
+        for (int j = 0; j < WT; ++j) {
+          acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ah, bh[j], acc[i][j], 0, 0, 0);
+          acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(al, bh[j], acc[i][j], 0, 0, 0);
+          if (kSplitB)
+            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ah, bl[kSplitB ? j : 0], acc[i][j], 0, 0, 0);
+        }
       }
     }
     __syncthreads();
@@ -540,13 +565,13 @@ __global__ __launch_bounds__(kWave * (kChMul + kChFeed)) void k_gemm_chain(
   }
 }
 
-template <int T, int AK, int BK, int EPI, int MAJOR>
+template <int T, int KB, int AK, int BK, int EPI, int MAJOR>
 void launch_gemm(hipStream_t st, const float* A, int64_t lda, const void* B, int64_t ldb, float* C, int64_t ldc,
                  const float* bias, const float* mask, int64_t ldm, float* db, int M, int N, int K) {
   const int tm = (int)ceil_div(M, T), tn = (int)ceil_div(N, T);
   const int major = MAJOR == kMajN ? tn : tm, minor = MAJOR == kMajN ? tm : tn;
-  hipLaunchKernelGGL((k_gemm<T, AK, BK, EPI, MAJOR>), dim3((unsigned)(align_up((size_t)major, 8) * minor)), dim3(256),
-                     0, st, A, lda, B, ldb, C, ldc, bias, mask, ldm, db, M, N, K, tm, tn);
+  hipLaunchKernelGGL((k_gemm<T, KB, AK, BK, EPI, MAJOR>), dim3((unsigned)(align_up((size_t)major, 8) * minor)),
+                     dim3(256), 0, st, A, lda, B, ldb, C, ldc, bias, mask, ldm, db, M, N, K, tm, tn);
 }
 
 template <int MT, int NT, int U, int EPI>
@@ -559,7 +584,7 @@ void launch_direct(hipStream_t st, const float* A, int64_t lda, const uint16_t* 
 // One forward layer.  Up to 64 rows, and wherever 64 x 64 tiles would give
 // fewer than one workgroup per CU, the direct kernel is the faster one (at 256
 // x 512 x 512 8 us against 32 us); from 512 workgroups on the larger tile is
-// (256 x 512 x 65536 66 us against 92 us).  The direct kernel takes several
+// (256 x 512 x 65536 66 us against 73 us).  The direct kernel takes several
 // row tiles per wave once that leaves two waves per SIMD, so that the weights
 // are read once.
 template <int EPI>
@@ -567,9 +592,9 @@ tide_status layer_fwd(hipStream_t st, const float* A, int64_t lda, const uint16_
                       int64_t ldc, const float* bias, int M, int N, int K) {
   if (ceil_div(M, 64) * ceil_div(N, 64) >= 256 && M > 64) {
     if (ceil_div(M, 128) * ceil_div(N, 128) >= 512)
-      launch_gemm<128, kA_KC, kB_WKC, EPI, kMajN>(st, A, lda, W, ldw, C, ldc, bias, nullptr, 0, nullptr, M, N, K);
+      launch_gemm<128, kBK, kA_KC, kB_WKC, EPI, kMajN>(st, A, lda, W, ldw, C, ldc, bias, nullptr, 0, nullptr, M, N, K);
     else
-      launch_gemm<64, kA_KC, kB_WKC, EPI, kMajN>(st, A, lda, W, ldw, C, ldc, bias, nullptr, 0, nullptr, M, N, K);
+      launch_gemm<64, kBK, kA_KC, kB_WKC, EPI, kMajN>(st, A, lda, W, ldw, C, ldc, bias, nullptr, 0, nullptr, M, N, K);
   } else if (M <= 16 || ceil_div(M, 16) * ceil_div(N, 16) < 2048) {
     launch_direct<1, 1, 8, EPI>(st, A, lda, W, ldw, C, ldc, bias, M, N, K);
   } else if (M <= 32) {
@@ -581,16 +606,22 @@ tide_status layer_fwd(hipStream_t st, const float* A, int64_t lda, const uint16_
   return TIDE_OK;
 }
 
-// dW = G^T a and the bias gradient db = column sums of G.  The larger tile
-// from 512 workgroups on, as in the forward.
-tide_status weight_grad(hipStream_t st, const float* G, int64_t ldg, const float* a, float* gW, float* gb, int n_out, int n_in,
-                        int batch) {
+// dW = G^T a and the bias gradient db = column sums of G.  The largest tile from
+// 512 workgroups on, as in the forward; 32 x 32 tiles up to four workgroups per
+// CU.  The whole backward at batch 256 with a last layer 2048 wide (1024
+// workgroups of 32 x 32) 101 us with either tile there, 4096 wide 131 us with
+// 64 x 64 and 133 us with 32 x 32.
+tide_status weight_grad(hipStream_t st, const float* G, int64_t ldg, const float* a, float* gW, float* gb, int n_out,
+                        int n_in, int batch) {
   if (ceil_div(n_out, 128) * ceil_div(n_in, 128) >= 512)
-    launch_gemm<128, kA_MC, kB_FNC, kE_STORE, kMajM>(st, G, ldg, a, n_in, gW, n_in, nullptr, nullptr, 0, gb, n_out,
-                                                     n_in, batch);
+    launch_gemm<128, kBK, kA_MC, kB_FNC, kE_STORE, kMajM>(st, G, ldg, a, n_in, gW, n_in, nullptr, nullptr, 0, gb,
+                                                          n_out, n_in, batch);
+  else if (ceil_div(n_out, 64) * ceil_div(n_in, 64) <= 256)
+    launch_gemm<32, 2 * kBK, kA_MC, kB_FNC, kE_STORE, kMajM>(st, G, ldg, a, n_in, gW, n_in, nullptr, nullptr, 0, gb,
+                                                             n_out, n_in, batch);
   else
-    launch_gemm<64, kA_MC, kB_FNC, kE_STORE, kMajM>(st, G, ldg, a, n_in, gW, n_in, nullptr, nullptr, 0, gb, n_out,
-                                                    n_in, batch);
+    launch_gemm<64, kBK, kA_MC, kB_FNC, kE_STORE, kMajM>(st, G, ldg, a, n_in, gW, n_in, nullptr, nullptr, 0, gb,
+                                                         n_out, n_in, batch);
   TIDE_LAUNCH_CHECK("mlp weight gradient");
   return TIDE_OK;
 }
@@ -601,8 +632,8 @@ tide_status weight_grad(hipStream_t st, const float* G, int64_t ldg, const float
 tide_status input_grad(hipStream_t st, const float* G, int64_t ldg, const uint16_t* W, const float* act, float* gx,
                        int64_t ldx, int n_out, int n_in, int batch) {
   if (ceil_div(batch, 128) * ceil_div(n_in, 128) >= 256) {
-    launch_gemm<128, kA_KC, kB_WNC, kE_MASK, kMajM>(st, G, ldg, W, n_in, gx, ldx, nullptr, act, n_in, nullptr, batch,
-                                                    n_in, n_out);
+    launch_gemm<128, kBK, kA_KC, kB_WNC, kE_MASK, kMajM>(st, G, ldg, W, n_in, gx, ldx, nullptr, act, n_in, nullptr,
+                                                         batch, n_in, n_out);
   } else {
     const int tm = (int)ceil_div(batch, kChM), tn = (int)ceil_div(n_in, kChN);
     const int sup_m = (int)ceil_div(tm, kChSup), sup_n = (int)ceil_div(tn, kChSup);

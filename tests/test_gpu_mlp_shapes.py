@@ -48,6 +48,7 @@ CASES = [
     ([16, 72, 16384], 33),         # direct kernel, 64-row tiles; 64 stages
     ([16, 520, 544], 64),          # input gradient with a cut last stage and a cut column tile
     ([16, 72, 8192], 65),          # 64 x 64 tiles forward, ragged rows
+    ([16, 136, 8224], 70),         # 64 x 64 tiles in the weight gradient, ragged every way
     ([16, 136, 65536], 129),       # 128 x 128 tiles forward and in the weight gradient, ragged both ways
     ([16, 16392, 64], 130),        # 128 x 128 tiles in the input gradient, ragged columns
 ]
