@@ -76,9 +76,9 @@ enum Major { kMajN = 0, kMajM = 1 };                 // the grid dimension sprea
 // loads each lane's eight operands of U chunks of K at once, so no LDS, no
 // barrier and one memory latency per U chunks.  It is the kernel for the
 // products that cannot fill the chip with LDS tiles: one row of poses
-// (512 -> 65536, 67 MB of weights read once: 15 us, 4.4 TB/s) and the hidden
-// layers (256 x 512 x 512: 8 us, 32 us with 64 x 64 tiles through LDS on 32
-// workgroups).
+// (512 -> 65536, 67 MB of weights read once: 13.7 us, 4.9 TB/s) and the hidden
+// layers (256 x 512 x 512: 7.6 us, 32 us with 64 x 64 tiles through LDS on 32
+// workgroups).  14.8 and 8.7 us with every load behind its own bounds check.
 // Requirements (checked by the host): K and the leading dimensions are
 // multiples of 8 and the bases 16-byte aligned, so a load is wholly inside
 // or wholly outside an operand.
@@ -96,29 +96,49 @@ __global__ __launch_bounds__(256) void k_gemm_direct(const float* __restrict__ A
   for (int i = 0; i < MT; ++i)
 #pragma unroll
     for (int j = 0; j < NT; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-  for (int k0 = 0; k0 < K; k0 += U * kBK) {
-    float4 a[U][MT][2];
-    uint4 b[U][NT];
+  // rows past the edges read the last one (their outputs are not stored); k past
+  // K, in the last round only, reads the last chunk for zeros
+  const uint16_t* pw[NT];
+  const float* pa[MT];
+#pragma unroll
+  for (int j = 0; j < NT; ++j) pw[j] = W + (int64_t)(n0 + 16 * j + r < N ? n0 + 16 * j + r : N - 1) * ldw;
+#pragma unroll
+  for (int i = 0; i < MT; ++i) pa[i] = A + (int64_t)(m0 + 16 * i + r < M ? m0 + 16 * i + r : M - 1) * lda;
+  float4 a[U][MT][2];
+  uint4 b[U][NT];
+  auto fetch = [&](int k0, bool tail) {
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      const int k = k0 + u * kBK + kc;
+      const int k1 = k0 + u * kBK + kc, k = !tail || k1 < K ? k1 : K - 8;
 #pragma unroll
-      for (int j = 0; j < NT; ++j) {
-        b[u][j] = make_uint4(0u, 0u, 0u, 0u);
-        const int n = n0 + 16 * j + r;
-        if (n < N && k < K) b[u][j] = *reinterpret_cast<const uint4*>(W + (int64_t)n * ldw + k);
-      }
+      for (int j = 0; j < NT; ++j) b[u][j] = *reinterpret_cast<const uint4*>(pw[j] + k);
 #pragma unroll
       for (int i = 0; i < MT; ++i) {
-        a[u][i][0] = a[u][i][1] = make_float4(0.f, 0.f, 0.f, 0.f);
-        const int m = m0 + 16 * i + r;
-        if (m < M && k < K) {
-          const float4* p = reinterpret_cast<const float4*>(A + (int64_t)m * lda + k);
-          a[u][i][0] = p[0];
-          a[u][i][1] = p[1];
-        }
+        a[u][i][0] = reinterpret_cast<const float4*>(pa[i] + k)[0];
+        a[u][i][1] = reinterpret_cast<const float4*>(pa[i] + k)[1];
       }
     }
+    if (!tail) return;
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const bool in = k0 + u * kBK + kc < K;
+#pragma unroll
+      for (int j = 0; j < NT; ++j)
+        b[u][j] = make_uint4(in ? b[u][j].x : 0u, in ? b[u][j].y : 0u, in ? b[u][j].z : 0u, in ? b[u][j].w : 0u);
+#pragma unroll
+      for (int i = 0; i < MT; ++i)
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+          const float4 x = a[u][i][h];
+          a[u][i][h] = make_float4(in ? x.x : 0.f, in ? x.y : 0.f, in ? x.z : 0.f, in ? x.w : 0.f);
+        }
+    }
+  };
+  for (int k0 = 0; k0 < K; k0 += U * kBK) {
+    if (k0 + U * kBK <= K)
+      fetch(k0, false);
+    else
+      fetch(k0, true);
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       if (k0 + u * kBK >= K) break;
@@ -583,7 +603,7 @@ void launch_direct(hipStream_t st, const float* A, int64_t lda, const uint16_t* 
 
 // One forward layer.  Up to 64 rows, and wherever 64 x 64 tiles would give
 // fewer than one workgroup per CU, the direct kernel is the faster one (at 256
-// x 512 x 512 8 us against 32 us); from 512 workgroups on the larger tile is
+// x 512 x 512 7.6 us against 32 us); from 512 workgroups on the larger tile is
 // (256 x 512 x 65536 66 us against 73 us).  The direct kernel takes several
 // row tiles per wave once that leaves two waves per SIMD, so that the weights
 // are read once.
