@@ -103,7 +103,12 @@ __global__ void __launch_bounds__(kWave * W) k_os_pass(const uint32_t* keys_in, 
   if (b0 >= n) return;
   const int m = (int)(n - b0 < kTile ? n - b0 : kTile);
   uint32_t key[R], val[R], rank[R];
-  tile_rank(keys_in, vals_in, n, b0, shift, L, key, val, rank);
+  const bool full = m == kTile;
+  const uint32_t *kt = keys_in + b0, *vt = vals_in ? vals_in + b0 : nullptr;
+  if (full)
+    tile_rank<true>(kt, vt, (uint32_t)b0, m, shift, L, key, val, rank);
+  else
+    tile_rank<false>(kt, vt, (uint32_t)b0, m, shift, L, key, val, rank);
   __syncthreads();
   const uint32_t cnt = tile_digit_offsets(L);
   // threads 0..255 own one digit each from here on
@@ -111,10 +116,13 @@ __global__ void __launch_bounds__(kWave * W) k_os_pass(const uint32_t* keys_in, 
   const bool dig = d < 256;
   unsigned long long* mine = status + t * 256 + d;
   if (dig) __hip_atomic_store(mine, (t == 0 ? kOsIncl : kOsAgg) | cnt, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  // the tile goes to LDS before the look-back, so its registers are free
+  // the keys go to LDS before the look-back, so their registers are free
   // while the look-back waits
   __syncthreads();
-  tile_stage(n, b0, shift, L, key, val, rank);
+  if (full)
+    tile_stage<true>(m, shift, L, key, rank);
+  else
+    tile_stage<false>(m, shift, L, key, rank);
   // this digit's count over all keys (its copies added up): a digit no key
   // holds needs no start, so its words stay aggregates of zero and no tile
   // walks back for it (most of the top byte's digits, say)
@@ -175,10 +183,13 @@ __global__ void __launch_bounds__(kWave * W) k_os_pass(const uint32_t* keys_in, 
   if (dig) {
     uint32_t gpre = 0;
     for (int q = 0; q < w; ++q) gpre += L.wsum[q];
-    L.gbase[d] = gpre + ginc - gc + excl;
+    L.gofs[d] = gpre + ginc - gc + excl - L.lstart[d];
   }
   __syncthreads();
-  tile_write(m, shift, L, out);
+  if (full)
+    tile_write<true>(m, shift, L, val, rank, out);
+  else
+    tile_write<false>(m, shift, L, val, rank, out);
 }
 
 template <int R, int W, typename LastOut>
@@ -215,8 +226,8 @@ void onesweep_run(uint32_t* ka, uint32_t* va, uint32_t* kb, uint32_t* vb, int64_
 // As radix_sort_pairs (bits <= 32, at most kOsMaxPasses passes) over tiles
 // of 64 W R keys (W waves of R rounds, W >= 4); n is the launch bound and
 // d_n, when given, the count on the device.  The last pass writes through
-// last_out(position, key, value) instead of the ping-pong buffer it would
-// fill (PairsOut over that buffer gives the sorted keys and values; another
+// last_out.key(position, key) and .val(position, value) instead of the ping-pong
+// buffer it would fill (PairsOut over that buffer gives the sorted keys and values; another
 // functor can write what the caller needs of each sorted pair instead), and
 // *keys_res / *vals_res name that buffer as if it had.
 template <int R, int W, typename LastOut>

@@ -341,40 +341,63 @@ __device__ __forceinline__ void hist_add(uint32_t* hw, uint32_t d, uint32_t c) {
 template <int R, int W = kSortWaves>
 struct TileLds {
   uint32_t wcnt[W][256];
-  uint32_t gbase[256], lstart[256], wsum[4];
-  alignas(16) uint32_t skey[kWave * W * R], sval[kWave * W * R];
+  uint32_t gofs[256], lstart[256], wsum[4];
+  alignas(16) uint32_t stage[kWave * W * R];   // the tile's keys, then its values
 };
 
-// Ranks the keys of tile [b0, b0 + 64 W R) ∩ [0, n) by digit (key >> shift)
-// & 255: wave w holds R rounds of 64 consecutive keys; rank[r] is the key's
-// rank among the keys of its digit held by the wave in earlier rounds and
-// lower lanes, and L.wcnt[w][d] ends as the wave's count of digit d.
+// A tile's phases are bound by the vector instructions they issue (208 per 64 keys
+// and pass in the first form, 101 now; k_radix_scatter has the times).  So:
+//   - kFull: the tile is full (its m elements are 64 W R), no lane is masked;
+//   - indices are 32 bits from the tile's first element;
+//   - the lanes of one digit are found by 8 ballots, each taking a bit's sign
+//     extension, a comparison and one three-operand instruction per half;
+//   - mbcnt gives the lanes below and adds the wave's earlier count.
+
+// Ranks the keys of the tile (its elements from keys, m of them) by digit
+// (key >> shift) & 255: wave w holds R rounds of 64 consecutive keys; rank[r] is
+// the key's rank among the keys of its digit held by the wave in earlier rounds
+// and lower lanes, and L.wcnt[w][d] ends as the wave's count of digit d.  Without
+// vals the values are the indices, from first on.
 // L.wcnt must be zero on entry; the caller synchronises afterwards.
-template <int R, int W>
-__device__ __forceinline__ void tile_rank(const uint32_t* keys_in, const uint32_t* vals_in, int64_t n, int64_t b0,
-                                          int shift, TileLds<R, W>& L, uint32_t* key, uint32_t* val, uint32_t* rank) {
-  const int w = threadIdx.x / kWave, lane = __lane_id();
-  const uint64_t lt = lanemask_lt();
-  const int64_t base = b0 + (int64_t)w * (kWave * R);
+template <bool kFull, int R, int W>
+__device__ __forceinline__ void tile_rank(const uint32_t* __restrict__ keys, const uint32_t* __restrict__ vals,
+                                          uint32_t first, int m, int shift, TileLds<R, W>& L, uint32_t* key,
+                                          uint32_t* val, uint32_t* rank) {
+  const uint32_t w = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave), lane = __lane_id();
+  const uint32_t base = w * (kWave * R) + lane;
 #pragma unroll
   for (int r = 0; r < R; ++r) {
-    const int64_t i = base + (int64_t)r * kWave + lane;
-    const bool ok = i < n;
-    key[r] = ok ? keys_in[i] : 0u;
-    val[r] = ok ? (vals_in ? vals_in[i] : (uint32_t)i) : 0u;
+    const uint32_t i = base + r * kWave;
+    key[r] = kFull || (int)i < m ? keys[i] : 0u;
+  }
+  if (vals) {
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      const uint32_t i = base + r * kWave;
+      val[r] = kFull || (int)i < m ? vals[i] : 0u;
+    }
+  } else {
+#pragma unroll
+    for (int r = 0; r < R; ++r) val[r] = first + base + r * kWave;
+  }
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    const bool ok = kFull || (int)(base + r * kWave) < m;
     const uint32_t d = (key[r] >> shift) & 255u;
-    uint64_t peers = __ballot(ok);
+    const uint64_t on = kFull ? ~0ull : __ballot(ok);
+    uint32_t plo = (uint32_t)on, phi = (uint32_t)(on >> 32);
 #pragma unroll
     for (int b = 0; b < 8; ++b) {
-      const bool bit = (d >> b) & 1u;
-      const uint64_t mk = __ballot(bit);
-      peers &= bit ? mk : ~mk;
+      const uint32_t x = (uint32_t)__builtin_amdgcn_sbfe((int)key[r], (uint32_t)(shift + b), 1u);   // the bit, in all places
+      const uint64_t mk = __ballot(x != 0u);
+      plo = __builtin_amdgcn_bitop3_b32(plo, (uint32_t)mk, x, 0x90);   // a & ~(b ^ c)
+      phi = __builtin_amdgcn_bitop3_b32(phi, (uint32_t)(mk >> 32), x, 0x90);
     }
-    uint32_t r0 = 0;
-    if (ok) r0 = L.wcnt[w][d];
-    rank[r] = r0 + (uint32_t)__popcll(peers & lt);
+    uint32_t* const c = &L.wcnt[w][d];
+    const uint32_t r0 = ok ? *c : 0u;
+    rank[r] = __builtin_amdgcn_mbcnt_hi(phi, __builtin_amdgcn_mbcnt_lo(plo, r0));
     // the lowest lane of each digit group advances the wave's counter
-    if (ok && (peers & lt) == 0) L.wcnt[w][d] = r0 + (uint32_t)__popcll(peers);
+    if (ok && rank[r] == r0) *c = r0 + (uint32_t)(__popc(plo) + __popc(phi));
   }
 }
 
@@ -405,34 +428,51 @@ __device__ __forceinline__ uint32_t tile_digit_offsets(TileLds<R, W>& L) {
   return cnt;
 }
 
-// Places the ranked keys in LDS in (digit, rank) order (L.lstart and L.wcnt
-// must be visible).
-template <int R, int W>
-__device__ __forceinline__ void tile_stage(int64_t n, int64_t b0, int shift, TileLds<R, W>& L, const uint32_t* key,
-                                           const uint32_t* val, const uint32_t* rank) {
-  const int w = threadIdx.x / kWave, lane = __lane_id();
-  const int64_t base = b0 + (int64_t)w * (kWave * R);
+// The ranked keys' places in (digit, rank) order, over rank[], and the keys in LDS
+// at those places (L.lstart and L.wcnt must be visible; the caller synchronises).
+template <bool kFull, int R, int W>
+__device__ __forceinline__ void tile_stage(int m, int shift, TileLds<R, W>& L, const uint32_t* key, uint32_t* rank) {
+  const uint32_t w = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+  const uint32_t base = w * (kWave * R) + __lane_id();
 #pragma unroll
   for (int r = 0; r < R; ++r) {
-    const int64_t i = base + (int64_t)r * kWave + lane;
-    if (i < n) {
+    if (kFull || (int)(base + r * kWave) < m) {
       const uint32_t dd = (key[r] >> shift) & 255u;
-      const uint32_t j = L.lstart[dd] + L.wcnt[w][dd] + rank[r];
-      L.skey[j] = key[r];
-      L.sval[j] = val[r];
+      rank[r] += L.lstart[dd] + L.wcnt[w][dd];
+      L.stage[rank[r]] = key[r];
     }
   }
 }
 
-// Writes the staged keys out to L.gbase[digit] + their place in the digit's
-// run, so a digit's run lands on consecutive addresses (L.gbase and the
-// staged keys must be visible): out(position, key, value) stores one.
-template <int R, int W, typename Out>
-__device__ __forceinline__ void tile_write(int m, int shift, const TileLds<R, W>& L, const Out& out) {
-  for (int j = threadIdx.x; j < m; j += kWave * W) {
-    const uint32_t k = L.skey[j];
-    const uint32_t dd = (k >> shift) & 255u;
-    out(L.gbase[dd] + (uint32_t)j - L.lstart[dd], k, L.sval[j]);
+// Writes the tile out, the element in place j to L.gofs[digit] + j: its digit's
+// start, less the digit's start in the tile, so a digit's run lands on consecutive
+// addresses (L.gofs and the staged keys must be visible): out.key(position, key),
+// then out.val(position, value).  Keys and values pass through the same LDS one
+// after the other: 27 KB instead of 43 KB, so four workgroups run on a CU instead
+// of three.
+template <bool kFull, int R, int W, typename Out>
+__device__ __forceinline__ void tile_write(int m, int shift, TileLds<R, W>& L, const uint32_t* val,
+                                           const uint32_t* place, const Out& out) {
+  uint32_t pos[R];
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    const int j = threadIdx.x + r * (kWave * W);
+    if (kFull || j < m) {
+      const uint32_t k = L.stage[j];
+      pos[r] = L.gofs[(k >> shift) & 255u] + (uint32_t)j;
+      out.key(pos[r], k);
+    }
+  }
+  __syncthreads();
+  const int base = (int)(threadIdx.x / kWave) * (kWave * R) + (int)__lane_id();
+#pragma unroll
+  for (int r = 0; r < R; ++r)
+    if (kFull || base + r * kWave < m) L.stage[place[r]] = val[r];
+  __syncthreads();
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    const int j = threadIdx.x + r * (kWave * W);
+    if (kFull || j < m) out.val(pos[r], L.stage[j]);
   }
 }
 
@@ -443,8 +483,8 @@ struct PairsOut {
   uint32_t* vals;
   const uint32_t* gather_src;
   uint32_t* gather_out;
-  __device__ void operator()(uint32_t pos, uint32_t k, uint32_t v) const {
-    keys[pos] = k;
+  __device__ void key(uint32_t pos, uint32_t k) const { keys[pos] = k; }
+  __device__ void val(uint32_t pos, uint32_t v) const {
     vals[pos] = v;
     if (gather_src) gather_out[pos] = gather_src[v];
   }

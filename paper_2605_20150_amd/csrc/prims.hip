@@ -36,8 +36,8 @@ __global__ void __launch_bounds__(1024) k_scan_partials(unsigned long long* part
 }
 
 // Per-tile digit histogram, digit-major for the scan or, by_tile, a tile's 256
-// counts together for scatters that add the counts up themselves.  Each wave counts into bins of its own, a
-// thread takes four consecutive keys per load (16 bytes when kVec: the keys
+// counts together for scatters that add the counts up themselves.  Each wave
+// counts into bins of its own, a thread takes four consecutive keys per load (16 bytes when kVec: the keys
 // are 16-byte aligned) and adds equal neighbouring digits as one run, and the
 // waves' bins are added at the end.  Workgroup b takes tiles b, b + G, ...
 // (G the grid), so a grid sized for a large capacity costs little when the
@@ -104,7 +104,11 @@ __global__ void __launch_bounds__(kSortThreads) k_radix_hist(const uint32_t* key
 
 // The scatter's 4096-key tiles as eight waves of eight rounds: a tile's
 // ranking is a chain of rounds, and eight waves ran the two tile-sort passes
-// over 14 M keys in 56.5 + 60.6 us against 61.4 + 66.8 us with four.
+// over 14 M keys in 56.5 + 60.6 us against 61.4 + 66.8 us with four.  Vector
+// instructions bound the pass: with 208 per 64 keys it took 815 us over 106.6 M
+// keys (tiles of 8192 892 us, with 16 waves 1037 us), with values staged after the
+// keys (27 KB of LDS instead of 43 KB, the CU's waves all in flight) 742 us, with
+// 101 per 64 keys 489 us, 2.6 TB/s; over 13.2 M keys 63 and now 44 us.
 constexpr int kScatterWaves = 8;
 constexpr int kScatterRounds = kSortTile / (kWave * kScatterWaves);
 
@@ -146,7 +150,7 @@ __global__ void __launch_bounds__(kWave * kScatterWaves) k_radix_scatter(const u
   __shared__ TileLds<kScatterRounds, kScatterWaves> L;
   for (int k = threadIdx.x; k < kScatterWaves * 256; k += kWave * kScatterWaves) (&L.wcnt[0][0])[k] = 0;
   if (kScan) {
-    if (threadIdx.x < 256) L.gbase[threadIdx.x] = gofs[(int64_t)threadIdx.x * nba + tile];
+    if (threadIdx.x < 256) L.gofs[threadIdx.x] = gofs[(int64_t)threadIdx.x * nba + tile];
   } else {
     // lane l of wave w: digits 4l .. 4l+3 of tiles w, w + 8, ...
     const int w = threadIdx.x / kWave, lane = __lane_id();
@@ -171,16 +175,18 @@ __global__ void __launch_bounds__(kWave * kScatterWaves) k_radix_scatter(const u
       }
     }
     // the staging space is free until the keys are ranked
-    reinterpret_cast<uint4*>(L.skey)[w * (256 / 4) + lane] = tot;
-    reinterpret_cast<uint4*>(L.sval)[w * (256 / 4) + lane] = pre;
+    static_assert(2 * kScatterWaves * 256 <= kSortTile, "both rows of counts per wave fit");
+    uint32_t *st = L.stage, *sp = L.stage + kScatterWaves * 256;
+    reinterpret_cast<uint4*>(st)[w * (256 / 4) + lane] = tot;
+    reinterpret_cast<uint4*>(sp)[w * (256 / 4) + lane] = pre;
     __syncthreads();
     const int d = threadIdx.x;
     uint32_t t = 0, p = 0, inc = 0;
     if (d < 256) {
 #pragma unroll
       for (int q = 0; q < kScatterWaves; ++q) {
-        t += L.skey[q * 256 + d];
-        p += L.sval[q * 256 + d];
+        t += st[q * 256 + d];
+        p += sp[q * 256 + d];
       }
       inc = wave_incl_scan(t);
       if (lane == kWave - 1) L.wsum[w] = inc;
@@ -189,18 +195,31 @@ __global__ void __launch_bounds__(kWave * kScatterWaves) k_radix_scatter(const u
     if (d < 256) {
       uint32_t lower = inc - t;
       for (int q = 0; q < w; ++q) lower += L.wsum[q];
-      L.gbase[d] = lower + p;
+      L.gofs[d] = lower + p;
     }
   }
   __syncthreads();
   uint32_t key[kScatterRounds], val[kScatterRounds], rank[kScatterRounds];
-  tile_rank(keys_in, vals_in, n, b0, shift, L, key, val, rank);
+  const bool full = m == kSortTile;
+  const uint32_t *kt = keys_in + b0, *vt = vals_in ? vals_in + b0 : nullptr;
+  if (full)
+    tile_rank<true>(kt, vt, (uint32_t)b0, m, shift, L, key, val, rank);
+  else
+    tile_rank<false>(kt, vt, (uint32_t)b0, m, shift, L, key, val, rank);
   __syncthreads();
   tile_digit_offsets(L);
+  if (threadIdx.x < 256) L.gofs[threadIdx.x] -= L.lstart[threadIdx.x];
   __syncthreads();
-  tile_stage(n, b0, shift, L, key, val, rank);
-  __syncthreads();
-  tile_write(m, shift, L, PairsOut{keys_out, vals_out, gather_src, gather_out});
+  const PairsOut out{keys_out, vals_out, gather_src, gather_out};
+  if (full) {
+    tile_stage<true>(m, shift, L, key, rank);
+    __syncthreads();
+    tile_write<true>(m, shift, L, val, rank, out);
+  } else {
+    tile_stage<false>(m, shift, L, key, rank);
+    __syncthreads();
+    tile_write<false>(m, shift, L, val, rank, out);
+  }
 }
 
 void radix_sort_pairs(uint32_t* ka, uint32_t* va, uint32_t* kb, uint32_t* vb, int64_t n, int bits,

@@ -359,7 +359,8 @@ struct PairRectOut {
   const uint32_t* rect;
   int64_t nv_max, n_pidx;
   uint32_t n_tiles, tiles_x;
-  __device__ void operator()(uint32_t pos, uint32_t, uint32_t r) const {
+  __device__ void key(uint32_t, uint32_t) const {}
+  __device__ void val(uint32_t pos, uint32_t r) const {
     r = (int64_t)r < nv_max ? r : 0u;   // in bounds even after a failed sort
     const uint2 q = *reinterpret_cast<const uint2*>(rect + 2 * (int64_t)r);
     const uint32_t x0 = q.x & 0xffff, y0 = q.x >> 16, x1 = q.y & 0xffff, y1 = q.y >> 16;
