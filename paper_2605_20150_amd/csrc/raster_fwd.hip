@@ -28,6 +28,8 @@ CamSet<T> make_camset(const tide_camera* cams, int n) {
     d.znear = (T)c.z_near; d.zfar = (T)c.z_far;
     d.limx = (T)(1.3 * 0.5 * c.width / c.fx);
     d.limy = (T)(1.3 * 0.5 * c.height / c.fy);
+    const double limx = d.limx, limy = d.limy;
+    d.reach = 3.03 * std::sqrt(c.fx * c.fx * (1 + limx * limx) + c.fy * c.fy * (1 + limy * limy));
     for (int k = 0; k < 3; ++k)
       d.pos[k] = (T)(-(c.R[k] * c.t[0] + c.R[3 + k] * c.t[1] + c.R[6 + k] * c.t[2]));
     d.W = c.width; d.H = c.height;
@@ -52,10 +54,13 @@ template CamSet<double> make_camset<double>(const tide_camera*, int);
 
 // ------------------------------------------------------------- preprocess
 // One thread per processing index.  The mean (12 B) is read first and every
-// camera's depth test runs on it; the other 56 columns are read only if some
-// camera keeps the Gaussian.  Columns of a block are contiguous, so lanes
-// (consecutive rows) read coalesced.  The camera-space position and the
-// pixel position are computed in double: at aerial scales (|p| ~ 300 m,
+// camera's depth test runs on it, then the scales and a bound of the footprint
+// against the image; the other 53 columns are read, and the footprint computed,
+// only for the Gaussians and cameras that are left.  Memory and vector issue
+// share the time: street level, 20M Gaussians, 4 cameras (30 % of the pairs in
+// view) 1145 us without the bound and 919 us with it; aerial, 1M, 4 cameras 79
+// and 73 us.  Columns of a block are contiguous, so lanes (consecutive rows)
+// read coalesced.  The camera-space position and the pixel position are computed in double: at aerial scales (|p| ~ 300 m,
 // f ~ 1700 px) single precision would put ~3e-4 px of error on u, v, which a
 // sub-pixel footprint turns into flipped alpha >= 1/255 decisions; rounding
 // the double result once leaves at most half an ulp of u.  This costs a few
@@ -63,6 +68,22 @@ template CamSet<double> make_camset<double>(const tide_camera*, int);
 __device__ inline double cam_depth(const double* Rd, const double* td, double m0, double m1, double m2) {
   return Rd[6] * m0 + Rd[7] * m1 + Rd[8] * m2 + td[2];
 }
+// Conservative test of a mean at camera depth pz against the image: false only
+// when the footprint's tile rectangle is surely empty.  The radius is 3 sqrt of
+// the largest eigenvalue of J S J^T + 0.3 I, at most 3 (|J|_F smax + sqrt 0.3) with
+// |J|_F pz <= sqrt(fx^2 (1 + limx^2) + fy^2 (1 + limy^2)) and smax the largest
+// scale; one per cent and 17 pixels (the round up to a whole radius and a tile)
+// cover the rounding of both sides.  Everything is multiplied by the depth: no
+// division.  NaN and infinite bounds pass.
+template <typename T>
+__device__ __forceinline__ bool may_meet_image(const DevCam<T>& cm, double m0, double m1, double m2, double pz, T smax) {
+  const double x = cm.fxd * (cm.Rd[0] * m0 + cm.Rd[1] * m1 + cm.Rd[2] * m2 + cm.td[0]) + cm.cxd * pz;
+  const double y = cm.fyd * (cm.Rd[3] * m0 + cm.Rd[4] * m1 + cm.Rd[5] * m2 + cm.td[1]) + cm.cyd * pz;
+  const double r = cm.reach * (double)smax + 18.7 * pz;   // 17 + 3.03 sqrt 0.3
+  const bool out = x + r < 0 || y + r < 0 || x - r > (double)(kTile * cm.Tx) * pz || y - r > (double)(kTile * cm.Ty) * pz;
+  return !(out && pz > 0);
+}
+
 template <typename T>
 __global__ void __launch_bounds__(256) k_preprocess(const T* __restrict__ params, const int32_t* __restrict__ order,
                                                     const int32_t* __restrict__ slot_rows, int32_t B,
@@ -87,11 +108,20 @@ __global__ void __launch_bounds__(256) k_preprocess(const T* __restrict__ params
       if (pz > (double)cm.znear && pz <= (double)cm.zfar) keep |= 1u << c;
     }
   }
+  T s0 = 0, s1 = 0, s2 = 0;
+  if (keep) {
+    s0 = Mth<T>::exp(P[3 * (int64_t)B]); s1 = Mth<T>::exp(P[4 * (int64_t)B]); s2 = Mth<T>::exp(P[5 * (int64_t)B]);
+    const T smax = s0 > s1 ? (s0 > s2 ? s0 : s2) : (s1 > s2 ? s1 : s2);
+#pragma unroll 1
+    for (int c = 0; c < ncam; ++c) {
+      const DevCam<T>& cm = cs.c[c];
+      const double m0 = mu[0], m1 = mu[1], m2 = mu[2];
+      if (!may_meet_image<T>(cm, m0, m1, m2, cam_depth(cm.Rd, cm.td, m0, m1, m2), smax)) keep &= ~(1u << c);
+    }
+  }
   uint32_t any = 0;
   if (keep) {
     // activations
-    const T s0 = Mth<T>::exp(P[3 * (int64_t)B]), s1 = Mth<T>::exp(P[4 * (int64_t)B]),
-            s2 = Mth<T>::exp(P[5 * (int64_t)B]);
     T qw = P[6 * (int64_t)B], qx = P[7 * (int64_t)B], qy = P[8 * (int64_t)B], qz = P[9 * (int64_t)B];
     const T qn = Mth<T>::sqrt(qw * qw + qx * qx + qy * qy + qz * qz);
     const T iq = (T)1 / qn;

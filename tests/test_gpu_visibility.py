@@ -1,0 +1,33 @@
+"""Which Gaussians a camera keeps: the preprocessing passes over a Gaussian on a bound
+of its footprint before it computes it, and must keep the same ones as the exact
+rule (the oracle's), for scales from far below a pixel to far above the image and
+means all around the camera."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_2605_20150_amd import synth
+from paper_2605_20150_amd.raster import Pool, Rasterizer
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("width,height,focal,shift", [(70, 41, 60.0, 0.0), (33, 5, 400.0, 25.0), (16, 16, 5.0, -40.0)])
+def test_kept_pairs(width, height, focal, shift):
+    """Both sides in double precision, so that no pair is decided by rounding."""
+    print(f"case: {width}x{height}, focal length {focal}, centre off by {shift}", flush=True)
+    n = 4000
+    rng = np.random.Generator(np.random.PCG64(51))
+    th = synth.dense_scene(n, 52).astype(np.float64)
+    th[:, 0:3] = rng.uniform(-1, 1, size=(n, 3)) * np.exp(rng.uniform(-2, 4, size=(n, 1)))
+    th[:, 3:6] = rng.uniform(-9, 4, size=(n, 1)) + rng.uniform(-1, 1, size=(n, 3))
+    cams = [synth.look_at(eye, (0, 0, 0), (0, 0, 1), width, height, focal, cx=width / 2 + shift, cy=height / 2 - shift)
+            for eye in ((2.5, 0.3, 0.4), (-20.0, 5.0, 3.0), (0.1, 0.0, 0.05))]
+    p = oracle.project(th, synth.cams_array(cams))
+    want = np.where(p["keep"], p["tiles_touched"], 0)
+    rast = Rasterizer("cuda")
+    proj = rast.preprocess(Pool.from_dense(torch.tensor(th, device="cuda"), 500), cams)
+    got = proj.tiles_touched.view(len(cams), -1)[:, :n].cpu().numpy()
+    assert 0.05 < (want > 0).mean() < 0.95
+    assert np.array_equal(got, want)
