@@ -278,6 +278,12 @@ __global__ void __launch_bounds__(64) k_render_bwd(const uint32_t* __restrict__ 
 template <typename T>
 constexpr int kBwdBatch = sizeof(T) == 4 ? 24 : 12;
 constexpr uint32_t kSplitTiles = 20 * 256;
+// Up to a tile per CU nothing shares a CU's LDS, and the batch is what one
+// workgroup may hold (a 32-bit mask in FP32): 16 tiles (1k, 64x64) 60 -> 56 us;
+// FP64, 63 tiles (2k dense, 133x97) with 12, 16, 20 and 24: 229, 214, 203, 195.
+template <typename T>
+constexpr int kBwdDeep = sizeof(T) == 4 ? 32 : 24;
+constexpr uint32_t kDeepTiles = 256;
 constexpr int kBwdGroup = 4;
 
 // x + its left neighbour's x, x = a b with the sum fused: the first step of
@@ -293,7 +299,7 @@ __device__ __forceinline__ float row_sum_prod_to_15(float a, float b) {
 }
 __device__ __forceinline__ double row_sum_prod_to_15(double a, double b) { return row_sum_to_15(a * b); }
 
-template <typename T>
+template <typename T, int NB>
 __global__ void __launch_bounds__(256) k_render_bwd_split(
     const uint32_t* __restrict__ order, const uint32_t* __restrict__ ranges, const uint32_t* __restrict__ inst_e,
     const uint32_t* __restrict__ inst_rec, const T* __restrict__ rec, int32_t Tx, int32_t Ty, int32_t W, int32_t H,
@@ -343,7 +349,6 @@ __global__ void __launch_bounds__(256) k_render_bwd_split(
     wmax = o > wmax ? o : wmax;
   }
   wmax = __builtin_amdgcn_readfirstlane(wmax);
-  constexpr int NB = kBwdBatch<T>;
   // per buffer (this batch's and the next one's), the entries' fields
   __shared__ T s_u[2][NB], s_v[2][NB], s_Ah[2][NB], s_Bh[2][NB], s_Ch[2][NB], s_A[2][NB], s_B[2][NB], s_C[2][NB],
       s_o[2][NB], s_r[2][NB], s_g[2][NB], s_b[2][NB], s_ka[2][NB], s_kc[2][NB], s_lim[2][NB];
@@ -1141,7 +1146,8 @@ static tide_status render_bwd_t(const tide_pool* pool, const tide_camera* cams, 
     TIDE_LAUNCH_CHECK("k_clear");
   }
   const bool split = grid <= kSplitTiles;
-  auto render = split ? k_render_bwd_split<T> : k_render_bwd<T>;
+  auto render = k_render_bwd<T>;
+  if (split) render = grid <= kDeepTiles ? k_render_bwd_split<T, kBwdDeep<T>> : k_render_bwd_split<T, kBwdBatch<T>>;
   TIDE_TIMED("render_bwd", st, hipLaunchKernelGGL(render, dim3(grid), dim3(split ? 4 * kWave : kWave), 0, st,
                      bins->tile_order, bins->ranges, bins->inst_e, bins->inst_rec, (const T*)proj->rec, bins->tiles_x, bins->tiles_y, fr->width,
                      fr->height, (T)bg[0], (T)bg[1], (T)bg[2], (const T*)fr->t_final, fr->last, (const T*)d_dimage,
