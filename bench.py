@@ -45,14 +45,14 @@ HBM_BOUND = ("preprocess", "reduce_pairs", "adjoint", "adam", "adjoint_adam", "l
 # counter reads for a plain 1 GiB device copy (x1.9999 and x1.0000), and the
 # hash of the kernel's sources when they were taken: the figure is reported
 # only while the sources are unchanged.
-TRAFFIC = {"render_bwd": {"bytes": 3957.3e6, "sources": ["raster_bwd.hip", "raster.h"],
-                          "sha256_16": "1620c5990e6483b0"}}
+TRAFFIC = {"render_bwd": {"bytes": 3499.6e6, "sources": ["raster_bwd.hip", "raster.h"],
+                          "sha256_16": "daa659ab5d02bb4c"}}
 # Executed-instruction view of the dominant kernel from one SQ counter pass
 # of this benchmark (profiles/render_aerial1M_sq_instructions.md): VALU
 # wave-instructions per launch and the busy cycles per VALU instruction of a
 # SIMD (4 cycles is one wave64 instruction back to back on a 16-lane SIMD),
 # reported while the kernel's sources are those the counters were taken on.
-ISSUE = {"render_bwd": {"valu_wave_instr": 705.6e6, "cycles_per_valu_per_simd": 3.82,
+ISSUE = {"render_bwd": {"valu_wave_instr": 681.2e6, "cycles_per_valu_per_simd": 3.48,
                         "sources": ["raster_bwd.hip", "raster.h"], "sha256_16": TRAFFIC["render_bwd"]["sha256_16"]}}
 # The step runs the backward's last stage and the masked Adam update as one
 # kernel (adjoint_adam); adjoint and adam are the same two stages as separate

@@ -109,7 +109,7 @@ class Pool:
             S = K + int(extra_slots)
             params = torch.empty((S, D, block_rows), dtype=theta.dtype, device=dev)
             sb, rows, order = (torch.empty((k,), dtype=torch.int32, device=dev) for k in (S, S, K))
-            L.check(L.load().tide_rows_to_blocks(C.c_void_p(theta.data_ptr()), N, block_rows, S,
+            L.check(L.load().tide_rows_to_blocks(C.c_void_p(theta.data_ptr()), N, int(block_rows), S,
                                                  _dtype_code(theta.dtype), C.c_void_p(params.data_ptr()),
                                                  C.c_void_p(sb.data_ptr()), C.c_void_p(rows.data_ptr()),
                                                  C.c_void_p(order.data_ptr()), C.c_void_p(_stream())))
@@ -372,7 +372,7 @@ def dense_grad(proj: Proj, grad: torch.Tensor, n: int) -> torch.Tensor:
         # one launch, and the host does not wait for the active rows' number
         out = torch.empty((n, D), dtype=grad.dtype, device=grad.device)
         pc = proj.c()
-        L.check(L.load().tide_dense_grad(C.byref(pc), C.c_void_p(grad.data_ptr()), grad.stride(0), n,
+        L.check(L.load().tide_dense_grad(C.byref(pc), C.c_void_p(grad.data_ptr()), grad.stride(0), int(n),
                                          C.c_void_p(out.data_ptr()), C.c_void_p(_stream())))
         return out
     act = proj.active[:n].bool()
