@@ -250,40 +250,46 @@ __global__ void __launch_bounds__(64) k_render_bwd(const uint32_t* __restrict__ 
   }
 }
 
-// The same adjoint with the tile split over four waves, for grids of few tiles:
-// there the launch waits for one wave's walk of the longest list (a chain of
-// dependent updates), not for arithmetic.  Wave q owns the pixel rows 4q .. 4q+3
-// (the q-th pixel of every lane above) and runs their recurrences over the
-// entries its rows may take, leaving three values per pixel and taken entry in
-// LDS (G, dL/dalpha and the colour weight); after every batch the waves share
-// its entries out, and each forms the sums over its entries' pixels.  Every sum
+// The same adjoint with eight waves to a tile, for grids of few tiles: there the
+// launch waits for one wave's walk of the longest list (a chain of dependent
+// updates), not for arithmetic.  Four waves walk: wave q owns the pixel rows
+// 4q .. 4q+3 (the q-th pixel of every lane above), runs their recurrences over
+// the entries its rows may take and leaves three values per pixel and taken
+// entry in LDS (G, dL/dalpha and the colour weight).  The other four form the
+// sums over the pixels, each of every fourth entry, of the batch before, stage
+// the next batch's entries and store the partials of the batch before that: a
+// pipeline with one barrier per batch, whose pace the recurrences set.  Every sum
 // is formed by the same operations in the same order as above (the fused ones
 // written out), so both give the same bits.
 //
-// The batch is what two workgroups per CU hold in LDS: a longer one spreads the
-// two barriers of a batch over more entries, a shorter one lets more workgroups
-// run.  One wave per tile against batches of 16, 24 and 32 (microseconds, FP32):
-//     16 tiles (1k Gaussians, 64x64)               108    69    60    58
-//    475 tiles (20k, dense, 400x300)               172   160   141   178
-//   1092 tiles (30k aerial, 4 x 330x200)          1665  1295  1127  1034
-//   4340 tiles (150k aerial, 2 x 979x546)          955   665   561   506
-//   5104 tiles (500k aerial, 4 x 700x450)         1870  1425  1215  1791
-//   5632 tiles (1M street level, 4 x 700x500)      685   638   790  1390
-//   8160 tiles (1M aerial, 1920x1080)              599   854  1064  1897
-// Past kSplitTiles (twenty tiles per CU) lists enough run at a time for the
-// single wave, which does less per entry, to be the faster one.  What the rule
-// gives away below it: dense lists of about one length (20k dense, 2 x 400x400,
-// 1250 tiles) take 204 instead of 186.  FP64 with batches of 12: 63 tiles (2k
-// dense, 133x97) 454 -> 260, 200 tiles 452 -> 281.
+// A batch of 12 lets two workgroups share a CU's LDS, one of 24 takes all of it
+// and spends a barrier on twice the entries.  The longer one is the faster where
+// a few long lists are what the launch waits for, the shorter one where all are
+// about as long: the kernels are launched one after the other and both look at
+// the longest list, first in the order; above 1.2 times a CU's share of all
+// entries (n_inst / 256) the tiles are the longer batch's, else the other's, and
+// the kernel they are not leaves at once (about 3 us).  Microseconds, FP32, one wave
+// per tile, then four waves that walk and sum in turn (batches of 24), then
+// batches of 12 and 24 here; [longest list x 256 / n_inst]:
+//     16 tiles (1k Gaussians, 64x64)               108    57    40    40  [37]
+//    475 tiles (20k, dense, 400x300)               172   138   115   126  [1.1]
+//   1092 tiles (30k aerial, 4 x 330x200)          1665  1125   938   773  [8.1]
+//   1250 tiles (20k, dense, 2 x 400x400)           186   200   168   217  [0.5]
+//   4000 tiles (out-of-core walk, 4 x 640x400)     100    96    92   148  [0.5]
+//   4340 tiles (150k aerial, 2 x 979x546)          955   564   456   356  [2.1]
+//   5104 tiles (500k aerial, 4 x 700x450)         1870  1213  1005  1257  [1.1]
+// FP64 (batches of 12, a workgroup per CU; before, batches of 24 in turn): 63
+// tiles (2k dense, 133x97) 454, 215, 161; 200 tiles 452, 232, 175.
+// Past kSplitTiles (twenty tiles per CU) enough lists run at a time for the single
+// wave per tile, which does less per entry, to be the faster one: 5800 tiles
+// (out-of-core walk, 4 x 800x450) 93 against 130 us here, 8160 (1M aerial,
+// 1920x1080) 600 against 900.
 template <typename T>
-constexpr int kBwdBatch = sizeof(T) == 4 ? 24 : 12;
-constexpr uint32_t kSplitTiles = 20 * 256;
-// Up to a tile per CU nothing shares a CU's LDS, and the batch is what one
-// workgroup may hold (a 32-bit mask in FP32): 16 tiles (1k, 64x64) 60 -> 56 us;
-// FP64, 63 tiles (2k dense, 133x97) with 12, 16, 20 and 24: 229, 214, 203, 195.
+constexpr int kBwdBatch = 12;
 template <typename T>
-constexpr int kBwdDeep = sizeof(T) == 4 ? 32 : 24;
-constexpr uint32_t kDeepTiles = 256;
+constexpr int kBwdLong = sizeof(T) == 4 ? 24 : 12;
+constexpr uint32_t kSplitTiles = 20 * 256, kLongTiles = 256;
+enum BwdPick { kAllTiles, kIfLong, kIfEven };
 constexpr int kBwdGroup = 4;
 
 // x + its left neighbour's x, x = a b with the sum fused: the first step of
@@ -300,62 +306,65 @@ __device__ __forceinline__ float row_sum_prod_to_15(float a, float b) {
 __device__ __forceinline__ double row_sum_prod_to_15(double a, double b) { return row_sum_to_15(a * b); }
 
 template <typename T, int NB>
-__global__ void __launch_bounds__(256) k_render_bwd_split(
+__global__ void __launch_bounds__(512) k_render_bwd_split(
     const uint32_t* __restrict__ order, const uint32_t* __restrict__ ranges, const uint32_t* __restrict__ inst_e,
     const uint32_t* __restrict__ inst_rec, const T* __restrict__ rec, int32_t Tx, int32_t Ty, int32_t W, int32_t H,
     T bg0, T bg1, T bg2, const T* __restrict__ tfin, const uint32_t* __restrict__ last_in, const T* __restrict__ dimg,
-    T* __restrict__ partial, uint8_t* __restrict__ taken, int mark_all) {
+    T* __restrict__ partial, uint8_t* __restrict__ taken, int mark_all, BwdPick pick, uint32_t n_inst) {
+  if (pick != kAllTiles) {
+    const uint32_t first = order[0], longest = ranges[2 * first + 1] - ranges[2 * first];
+    const bool is_long = (uint64_t)longest * (256 * 5) > (uint64_t)n_inst * 6;
+    if (is_long != (pick == kIfLong)) return;
+  }
   const int nt = Tx * Ty;
   const int g = (int)order[blockIdx.x];
   const int c = g / nt, t = g - c * nt;
   const int tx = t % Tx, ty = t / Tx;
-  const int tid = threadIdx.x, lane = __lane_id(), w = __builtin_amdgcn_readfirstlane(tid / kWave);
+  const int tid = threadIdx.x, lane = __lane_id(), wave = __builtin_amdgcn_readfirstlane(tid / kWave);
+  const bool walks = wave < 4;   // the waves that run the recurrences; the others form the sums
+  const int w = wave & 3;
   const int px = tx * kTile + (lane & 15), py0 = ty * kTile + (lane >> 4), py = py0 + 4 * w;
   const T fxp = (T)px + (T)0.5, fyp = (T)py + (T)0.5;
   const int64_t HW = (int64_t)H * W;
   const bool odd = (lane & 1) != 0;
-  T Tr = 1, Pb = 0;
-  uint32_t lst = 0;
-  // dL/dpixel of the lane's four pixels (one in each wave's rows), red and green
-  // swapped in odd lanes (row_pair_sum_to_15)
-  T g0[4], g1[4], g2[4];
-#pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    g0[q] = g1[q] = g2[q] = 0;
+  // per slot of a batch (the one staged, walked, summed and stored), the entries' fields
+  __shared__ T s_u[4][NB], s_v[4][NB], s_Ah[4][NB], s_Bh[4][NB], s_Ch[4][NB], s_A[4][NB], s_B[4][NB], s_C[4][NB],
+      s_o[4][NB], s_r[4][NB], s_g[4][NB], s_b[4][NB], s_ka[4][NB], s_kc[4][NB], s_lim[4][NB];
+  __shared__ uint32_t s_e[4][NB], s_took[4][4], s_max[4];
+  __shared__ T s_G[2][NB][4][kWave], s_d[2][NB][4][kWave], s_w[2][NB][4][kWave];
+  __shared__ T s_part[2][NB][4][kG2];   // per entry, the sums of the four lane rows
+  // dL/dpixel of pixel q of the lane, red and green swapped in odd lanes (row_pair_sum_to_15)
+  auto upstream = [&](int q, T& x0, T& x1, T& x2) {
+    x0 = x1 = x2 = 0;
     if (px < W && py0 + 4 * q < H) {
       const int64_t p = (int64_t)(py0 + 4 * q) * W + px;
-      g0[q] = dimg[((int64_t)c * 3 + 0) * HW + p];
-      g1[q] = dimg[((int64_t)c * 3 + 1) * HW + p];
-      g2[q] = dimg[((int64_t)c * 3 + 2) * HW + p];
+      x0 = dimg[((int64_t)c * 3 + 0) * HW + p];
+      x1 = dimg[((int64_t)c * 3 + 1) * HW + p];
+      x2 = dimg[((int64_t)c * 3 + 2) * HW + p];
     }
-    if (q == w) Pb = -Mth<T>::fma(bg2, g2[q], Mth<T>::fma(bg1, g1[q], bg0 * g0[q]));
-    const T a = g0[q], b = g1[q];
-    g0[q] = odd ? b : a;
-    g1[q] = odd ? a : b;
-  }
-  T h0 = 0, h1 = 0, h2 = 0;   // this wave's pixel's
+  };
+  T Tr = 1, Pb = 0, h0 = 0, h1 = 0, h2 = 0;
+  uint32_t lst = 0, wmax = 0;
+  if (walks) {
+    upstream(w, h0, h1, h2);
+    Pb = -Mth<T>::fma(bg2, h2, Mth<T>::fma(bg1, h1, bg0 * h0));
+    const T x = h0, y = h1;
+    h0 = odd ? y : x;
+    h1 = odd ? x : y;
+    if (px < W && py < H) {
+      const int64_t p = (int64_t)py * W + px;
+      Tr = tfin[(int64_t)c * HW + p];
+      lst = last_in[(int64_t)c * HW + p];
+    }
+    wmax = lst;   // the list's length as this wave's pixels see it
 #pragma unroll
-  for (int q = 0; q < 4; ++q)
-    if (q == w) { h0 = g0[q]; h1 = g1[q]; h2 = g2[q]; }
-  if (px < W && py < H) {
-    const int64_t p = (int64_t)py * W + px;
-    Tr = tfin[(int64_t)c * HW + p];
-    lst = last_in[(int64_t)c * HW + p];
+    for (int off = 32; off >= 1; off >>= 1) {
+      const uint32_t o = __shfl_xor(wmax, off, kWave);
+      wmax = o > wmax ? o : wmax;
+    }
+    wmax = __builtin_amdgcn_readfirstlane(wmax);
+    if (lane == 0) s_max[w] = wmax;
   }
-  uint32_t wmax = lst;   // the list's length as this wave's pixels see it
-#pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) {
-    const uint32_t o = __shfl_xor(wmax, off, kWave);
-    wmax = o > wmax ? o : wmax;
-  }
-  wmax = __builtin_amdgcn_readfirstlane(wmax);
-  // per buffer (this batch's and the next one's), the entries' fields
-  __shared__ T s_u[2][NB], s_v[2][NB], s_Ah[2][NB], s_Bh[2][NB], s_Ch[2][NB], s_A[2][NB], s_B[2][NB], s_C[2][NB],
-      s_o[2][NB], s_r[2][NB], s_g[2][NB], s_b[2][NB], s_ka[2][NB], s_kc[2][NB], s_lim[2][NB];
-  __shared__ T s_G[NB][4][kWave], s_d[NB][4][kWave], s_w[NB][4][kWave];
-  __shared__ T s_part[NB][4][kG2];   // per entry, the sums of the four lane rows
-  __shared__ uint32_t s_took[4], s_max[4];
-  if (lane == 0) s_max[w] = wmax;
   __syncthreads();
   uint32_t maxl = s_max[0];
 #pragma unroll
@@ -364,140 +373,169 @@ __global__ void __launch_bounds__(256) k_render_bwd_split(
   const uint32_t start = ranges[2 * g];
   if (mark_all) {
     const uint32_t end = ranges[2 * g + 1];
-    for (uint32_t j = start + maxl + tid; j < end; j += 256) taken[inst_e[j]] = 0;
+    for (uint32_t j = start + maxl + tid; j < end; j += 512) taken[inst_e[j]] = 0;
   }
   const T ks = (T)Ex<T>::k;
-  auto below = [](uint32_t hi) { return hi > (uint32_t)NB ? hi - NB : 0u; };   // a batch covers [below(hi), hi)
-  // wave 0 stages the entries, loaded a batch ahead; wave 3 stores the partials
+  // batch i covers the entries [lo_of(i), hi_of(i)), from the back
+  const int n_batch = (int)((maxl + NB - 1) / NB);
+  auto hi_of = [&](int i) { return maxl - (uint32_t)i * NB; };
+  auto lo_of = [&](int i) { return hi_of(i) > (uint32_t)NB ? hi_of(i) - NB : 0u; };
+
+  if (walks) {
+    __syncthreads();   // batch 0 is staged
+    for (int it = 0; it < n_batch + 2; ++it) {
+      if (it < n_batch) {
+        const uint32_t lo = lo_of(it);
+        const int n = (int)(hi_of(it) - lo), sl = it & 3, buf = it & 1;
+        bool may = false;
+        if (lane < n && lo + lane < wmax)
+          may = box_may_take<kTile, 4, T>(s_u[sl][lane], s_v[sl][lane], s_Ah[sl][lane], s_Bh[sl][lane], s_Ch[sl][lane],
+                                          s_ka[sl][lane], s_kc[sl][lane], s_lim[sl][lane], tx * kTile,
+                                          ty * kTile + 4 * w);
+        uint32_t own = (uint32_t)__ballot(may), took = 0;
+        while (own != 0) {
+          // alphas first, of entries that do not depend on each other
+          int k[kBwdGroup];
+          T G[kBwdGroup], araw[kBwdGroup];
+          uint64_t pm[kBwdGroup], any = 0;
+#pragma unroll
+          for (int i = 0; i < kBwdGroup; ++i) {
+            const bool some = own != 0;
+            k[i] = some ? 31 - (int)__builtin_clz(own) : 0;
+            own &= ~(some ? 1u << k[i] : 0u);
+            const T dx = fxp - s_u[sl][k[i]], dy = fyp - s_v[sl][k[i]];
+            bool in_power, in_alpha;
+            entry_alpha_tests<T>(s_Ah[sl][k[i]] * dx * dx, s_Bh[sl][k[i]] * dx, s_Ch[sl][k[i]], s_o[sl][k[i]], dy, G[i],
+                                 araw[i], in_power, in_alpha);
+            pm[i] = __ballot(in_power) & __ballot(in_alpha) & __ballot(lo + (uint32_t)k[i] < lst);
+            pm[i] = some ? pm[i] : 0;
+            any |= pm[i];
+          }
+          if (any == 0) continue;
+#pragma unroll
+          for (int i = 0; i < kBwdGroup; ++i) {
+            if (pm[i] == 0) continue;
+            // alpha clamped at 0.99 has no input dependence
+            const T a_ok = lane_bit(pm[i]) ? Mth<T>::clamp(araw[i], (T)0, (T)0.99) : (T)0;
+            const T G_ok = lane_bit(pm[i] & __ballot(araw[i] < (T)0.99)) ? G[i] : (T)0;
+            const T cr = s_r[sl][k[i]], cg = s_g[sl][k[i]], cb = s_b[sl][k[i]];
+            const T c0 = odd ? cg : cr, c1 = odd ? cr : cg;   // in the lane's h0 / h1 order
+            Tr *= Mth<T>::rcp_fast((T)1 - a_ok);
+            const T e = Mth<T>::fma(c0, h0, Mth<T>::fma(c1, h1, Mth<T>::fma(cb, h2, Pb)));
+            Pb = Mth<T>::fma(-a_ok, e, Pb);
+            s_G[buf][k[i]][w][lane] = G_ok;
+            s_d[buf][k[i]][w][lane] = Tr * e;
+            s_w[buf][k[i]][w][lane] = a_ok * Tr;
+            took |= 1u << k[i];
+          }
+        }
+        if (lane == 0) s_took[sl][w] = took;
+      }
+      __syncthreads();
+    }
+    return;
+  }
+
+  T g0[4], g1[4], g2[4];
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    T x, y;
+    upstream(q, x, y, g2[q]);
+    g0[q] = odd ? y : x;
+    g1[q] = odd ? x : y;
+  }
+  // the first summing wave stages the entries, loaded a batch ahead; the last one stores the partials
   T f[9];
-  auto load = [&](uint32_t hi) {
-    const uint32_t lo = below(hi);
-    if ((uint32_t)lane < hi - lo) {
-      const T* q = rec + (int64_t)inst_rec[inst_e[start + lo + lane]] * kRec;
+  uint32_t e_next = 0;
+  auto load = [&](int i) {
+    const uint32_t lo = lo_of(i);
+    if ((uint32_t)lane < hi_of(i) - lo) {
+      e_next = inst_e[start + lo + lane];
+      const T* q = rec + (int64_t)inst_rec[e_next] * kRec;
 #pragma unroll
       for (int m = 0; m < 9; ++m) f[m] = q[m];
     }
   };
-  auto stage = [&](uint32_t hi, int buf) {
-    if ((uint32_t)lane < hi - below(hi)) {
-      s_u[buf][lane] = f[0]; s_v[buf][lane] = f[1];
-      s_A[buf][lane] = f[2]; s_B[buf][lane] = f[3]; s_C[buf][lane] = f[4];
-      s_Ah[buf][lane] = (T)-0.5 * ks * f[2]; s_Bh[buf][lane] = -ks * f[3]; s_Ch[buf][lane] = (T)-0.5 * ks * f[4];
-      box_prepare<T>(f[2], f[3], f[4], f[5], s_ka[buf][lane], s_kc[buf][lane], s_lim[buf][lane]);
-      s_o[buf][lane] = f[5]; s_r[buf][lane] = f[6]; s_g[buf][lane] = f[7]; s_b[buf][lane] = f[8];
+  auto stage = [&](int i) {
+    const int sl = i & 3;
+    if ((uint32_t)lane < hi_of(i) - lo_of(i)) {
+      s_e[sl][lane] = e_next;
+      s_u[sl][lane] = f[0]; s_v[sl][lane] = f[1];
+      s_A[sl][lane] = f[2]; s_B[sl][lane] = f[3]; s_C[sl][lane] = f[4];
+      s_Ah[sl][lane] = (T)-0.5 * ks * f[2]; s_Bh[sl][lane] = -ks * f[3]; s_Ch[sl][lane] = (T)-0.5 * ks * f[4];
+      box_prepare<T>(f[2], f[3], f[4], f[5], s_ka[sl][lane], s_kc[sl][lane], s_lim[sl][lane]);
+      s_o[sl][lane] = f[5]; s_r[sl][lane] = f[6]; s_g[sl][lane] = f[7]; s_b[sl][lane] = f[8];
     }
-    if (below(hi) > 0) load(below(hi));
+    if (i + 1 < n_batch) load(i + 1);
   };
-  if (w == 0 && maxl > 0) {
-    load(maxl);
-    stage(maxl, 0);
+  if (w == 0 && n_batch > 0) {
+    load(0);
+    stage(0);
   }
   __syncthreads();
-  int buf = 0;
-  for (uint32_t hi = maxl; hi > 0; hi = below(hi), buf ^= 1) {
-    const uint32_t lo = below(hi);
-    const int n = (int)(hi - lo);
-    uint32_t my_e = 0;
-    if (w == 3 && lane < n) my_e = inst_e[start + lo + lane];
-    bool may = false;
-    if (lane < n && lo + lane < wmax)
-      may = box_may_take<kTile, 4, T>(s_u[buf][lane], s_v[buf][lane], s_Ah[buf][lane], s_Bh[buf][lane], s_Ch[buf][lane],
-                                      s_ka[buf][lane], s_kc[buf][lane], s_lim[buf][lane], tx * kTile, ty * kTile + 4 * w);
-    // 1. the recurrences over the wave's entries, from the back
-    uint32_t own = (uint32_t)__ballot(may), took = 0;
-    while (own != 0) {
-      // alphas first, of entries that do not depend on each other
-      int k[kBwdGroup];
-      T G[kBwdGroup], araw[kBwdGroup];
-      uint64_t pm[kBwdGroup], any = 0;
-#pragma unroll
-      for (int i = 0; i < kBwdGroup; ++i) {
-        const bool some = own != 0;
-        k[i] = some ? 31 - (int)__builtin_clz(own) : 0;
-        own &= ~(some ? 1u << k[i] : 0u);
-        const T dx = fxp - s_u[buf][k[i]], dy = fyp - s_v[buf][k[i]];
-        bool in_power, in_alpha;
-        entry_alpha_tests<T>(s_Ah[buf][k[i]] * dx * dx, s_Bh[buf][k[i]] * dx, s_Ch[buf][k[i]], s_o[buf][k[i]], dy, G[i],
-                             araw[i], in_power, in_alpha);
-        pm[i] = __ballot(in_power) & __ballot(in_alpha) & __ballot(lo + (uint32_t)k[i] < lst);
-        pm[i] = some ? pm[i] : 0;
-        any |= pm[i];
-      }
-      if (any == 0) continue;
-#pragma unroll
-      for (int i = 0; i < kBwdGroup; ++i) {
-        if (pm[i] == 0) continue;
-        // alpha clamped at 0.99 has no input dependence
-        const T a_ok = lane_bit(pm[i]) ? Mth<T>::clamp(araw[i], (T)0, (T)0.99) : (T)0;
-        const T G_ok = lane_bit(pm[i] & __ballot(araw[i] < (T)0.99)) ? G[i] : (T)0;
-        const T cr = s_r[buf][k[i]], cg = s_g[buf][k[i]], cb = s_b[buf][k[i]];
-        const T c0 = odd ? cg : cr, c1 = odd ? cr : cg;   // in the lane's h0 / h1 order
-        Tr *= Mth<T>::rcp_fast((T)1 - a_ok);
-        const T e = Mth<T>::fma(c0, h0, Mth<T>::fma(c1, h1, Mth<T>::fma(cb, h2, Pb)));
-        Pb = Mth<T>::fma(-a_ok, e, Pb);
-        s_G[k[i]][w][lane] = G_ok;
-        s_d[k[i]][w][lane] = Tr * e;
-        s_w[k[i]][w][lane] = a_ok * Tr;
-        took |= 1u << k[i];
-      }
-    }
-    if (lane == 0) s_took[w] = took;
-    __syncthreads();
-    // 2. the sums over the pixels, of every fourth entry
-    if (w == 0 && lo > 0) stage(lo, buf ^ 1);
-    uint32_t h[4], hit = 0;
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      h[q] = __builtin_amdgcn_readfirstlane(s_took[q]);
-      hit |= h[q];
-    }
-    for (uint32_t todo = hit & (0x11111111u << w); todo != 0; todo &= todo - 1) {
-      const int k = __builtin_ctz(todo);
-      const T v = s_v[buf][k], dx = fxp - s_u[buf][k];
-      T S0 = 0, S1 = 0, S2 = 0, a_0 = 0, a_1 = 0, a_b = 0;
+  for (int it = 0; it < n_batch + 2; ++it) {
+    if (w == 0 && it + 1 < n_batch) stage(it + 1);
+    if (it >= 1 && it <= n_batch) {   // the sums over the pixels, of every fourth entry of the batch before
+      const int sl = (it - 1) & 3, buf = (it - 1) & 1;
+      uint32_t h[4], hit = 0;
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
-        if (!((h[q] >> k) & 1u)) continue;
-        const T dy = (T)(py0 + 4 * q) + (T)0.5 - v;
-        const T Gq = s_G[k][q][lane], dal = s_d[k][q][lane], wq = s_w[k][q][lane];
-        a_0 = Mth<T>::fma(wq, g0[q], a_0);
-        a_1 = Mth<T>::fma(wq, g1[q], a_1);
-        a_b = Mth<T>::fma(wq, g2[q], a_b);
-        const T tq = Gq * dal;
-        S0 = Mth<T>::fma(Gq, dal, S0);
-        const T tdy = tq * dy;
-        S1 = Mth<T>::fma(tq, dy, S1);
-        S2 = Mth<T>::fma(tdy, dy, S2);
+        h[q] = __builtin_amdgcn_readfirstlane(s_took[sl][q]);
+        hit |= h[q];
       }
-      T p1 = dx * S0, q_r, q_g;
-      const T a_A = row_sum_prod_to_15(dx, p1), a_B = row_sum_prod_to_15(dx, S1);
-      p1 = row_sum_prod_to_15(dx, S0);
-      S1 = row_sum_to_15(S1);
-      S2 = row_sum_to_15(S2);
-      S0 = row_sum_to_15(S0);
-      row_pair_sum_to_15(a_0, a_1, q_r, q_g);
-      a_b = row_sum_to_15(a_b);
-      if ((lane & 15) == 15) {
-        T* S = s_part[k][lane >> 4];
-        S[0] = p1; S[1] = S1; S[2] = a_A; S[3] = a_B; S[4] = S2;
-        S[5] = S0; S[6] = q_r; S[7] = q_g; S[8] = a_b;
+      for (uint32_t todo = hit & (0x11111111u << w); todo != 0; todo &= todo - 1) {
+        const int k = __builtin_ctz(todo);
+        const T v = s_v[sl][k], dx = fxp - s_u[sl][k];
+        T S0 = 0, S1 = 0, S2 = 0, a_0 = 0, a_1 = 0, a_b = 0;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          if (!((h[q] >> k) & 1u)) continue;
+          const T dy = (T)(py0 + 4 * q) + (T)0.5 - v;
+          const T Gq = s_G[buf][k][q][lane], dal = s_d[buf][k][q][lane], wq = s_w[buf][k][q][lane];
+          a_0 = Mth<T>::fma(wq, g0[q], a_0);
+          a_1 = Mth<T>::fma(wq, g1[q], a_1);
+          a_b = Mth<T>::fma(wq, g2[q], a_b);
+          const T tq = Gq * dal;
+          S0 = Mth<T>::fma(Gq, dal, S0);
+          const T tdy = tq * dy;
+          S1 = Mth<T>::fma(tq, dy, S1);
+          S2 = Mth<T>::fma(tdy, dy, S2);
+        }
+        T p1 = dx * S0, q_r, q_g;
+        const T a_A = row_sum_prod_to_15(dx, p1), a_B = row_sum_prod_to_15(dx, S1);
+        p1 = row_sum_prod_to_15(dx, S0);
+        S1 = row_sum_to_15(S1);
+        S2 = row_sum_to_15(S2);
+        S0 = row_sum_to_15(S0);
+        row_pair_sum_to_15(a_0, a_1, q_r, q_g);
+        a_b = row_sum_to_15(a_b);
+        if ((lane & 15) == 15) {
+          T* S = s_part[buf][k][lane >> 4];
+          S[0] = p1; S[1] = S1; S[2] = a_A; S[3] = a_B; S[4] = S2;
+          S[5] = S0; S[6] = q_r; S[7] = q_g; S[8] = a_b;
+        }
+      }
+    }
+    if (w == 3 && it >= 2) {   // the partials of the batch before that
+      const int sl = (it - 2) & 3, buf = it & 1;
+      const uint32_t hit = s_took[sl][0] | s_took[sl][1] | s_took[sl][2] | s_took[sl][3];
+      if ((uint32_t)lane < hi_of(it - 2) - lo_of(it - 2)) {
+        const uint32_t my_e = s_e[sl][lane];
+        if ((hit >> lane) & 1u) {
+          Rec9<T> r;
+#pragma unroll
+          for (int m = 0; m < kG2; ++m)
+            r.v[m] = (s_part[buf][lane][0][m] + s_part[buf][lane][1][m]) +
+                     (s_part[buf][lane][2][m] + s_part[buf][lane][3][m]);
+          entry_factors<T>(s_o[sl][lane], s_A[sl][lane], s_B[sl][lane], s_C[sl][lane], r);
+          *reinterpret_cast<Rec9<T>*>(partial + (int64_t)my_e * kG2) = r;
+          taken[my_e] = 1;
+        } else if (mark_all) {
+          taken[my_e] = 0;
+        }
       }
     }
     __syncthreads();
-    // 3. the partials (the other waves go on with the next batch)
-    if (w == 3 && lane < n) {
-      if ((hit >> lane) & 1u) {
-        Rec9<T> r;
-#pragma unroll
-        for (int m = 0; m < kG2; ++m)
-          r.v[m] = (s_part[lane][0][m] + s_part[lane][1][m]) + (s_part[lane][2][m] + s_part[lane][3][m]);
-        entry_factors<T>(s_o[buf][lane], s_A[buf][lane], s_B[buf][lane], s_C[buf][lane], r);
-        *reinterpret_cast<Rec9<T>*>(partial + (int64_t)my_e * kG2) = r;
-        taken[my_e] = 1;
-      } else if (mark_all) {
-        taken[my_e] = 0;
-      }
-    }
   }
 }
 
@@ -1145,13 +1183,26 @@ static tide_status render_bwd_t(const tide_pool* pool, const tide_camera* cams, 
     hipLaunchKernelGGL(k_clear, dim3((uint32_t)(nb < 4096 ? nb : 4096)), dim3(256), 0, st, w.taken, w.n_clear);
     TIDE_LAUNCH_CHECK("k_clear");
   }
-  const bool split = grid <= kSplitTiles;
-  auto render = k_render_bwd<T>;
-  if (split) render = grid <= kDeepTiles ? k_render_bwd_split<T, kBwdDeep<T>> : k_render_bwd_split<T, kBwdBatch<T>>;
-  TIDE_TIMED("render_bwd", st, hipLaunchKernelGGL(render, dim3(grid), dim3(split ? 4 * kWave : kWave), 0, st,
-                     bins->tile_order, bins->ranges, bins->inst_e, bins->inst_rec, (const T*)proj->rec, bins->tiles_x, bins->tiles_y, fr->width,
-                     fr->height, (T)bg[0], (T)bg[1], (T)bg[2], (const T*)fr->t_final, fr->last, (const T*)d_dimage,
-                     w.partial, w.taken, mark_all));
+  auto split = [&](auto kernel, BwdPick pick) {
+    hipLaunchKernelGGL(kernel, dim3(grid), dim3(8 * kWave), 0, st, bins->tile_order, bins->ranges, bins->inst_e,
+                       bins->inst_rec, (const T*)proj->rec, bins->tiles_x, bins->tiles_y, fr->width, fr->height,
+                       (T)bg[0], (T)bg[1], (T)bg[2], (const T*)fr->t_final, fr->last, (const T*)d_dimage, w.partial,
+                       w.taken, mark_all, pick, (uint32_t)ni);
+  };
+  auto render = [&]() {
+    if (grid > kSplitTiles) {
+      hipLaunchKernelGGL(k_render_bwd<T>, dim3(grid), dim3(kWave), 0, st, bins->tile_order, bins->ranges, bins->inst_e,
+                         bins->inst_rec, (const T*)proj->rec, bins->tiles_x, bins->tiles_y, fr->width, fr->height,
+                         (T)bg[0], (T)bg[1], (T)bg[2], (const T*)fr->t_final, fr->last, (const T*)d_dimage, w.partial,
+                         w.taken, mark_all);
+    } else if (grid <= kLongTiles || kBwdLong<T> == kBwdBatch<T>) {
+      split(k_render_bwd_split<T, kBwdLong<T>>, kAllTiles);   // nothing shares a CU
+    } else {
+      split(k_render_bwd_split<T, kBwdLong<T>>, kIfLong);
+      split(k_render_bwd_split<T, kBwdBatch<T>>, kIfEven);
+    }
+  };
+  TIDE_TIMED("render_bwd", st, render());
   TIDE_LAUNCH_CHECK("k_render_bwd");
   if (bins->n_vis > 0 && ni > 0) {
     const bool whole = (int64_t)bins->tiles_x * bins->tiles_y <= kWholeTiles || w.pieces == 1;

@@ -46,17 +46,18 @@ def test_image_contributors_and_gradient(width, height, n, logit):
 
 
 @pytest.mark.parametrize("dtype,rtol", [(torch.float32, 2e-4), (torch.float64, 5e-13)])
-@pytest.mark.parametrize("n", [25, 400])
-def test_backward_of_few_and_of_many_tiles(n, dtype, rtol):
-    """The two backward compositing kernels (four waves a tile in small grids, one
-    in large ones: over 5120 tiles) form every entry's sums by the same operations
-    in the same order: 8 views of 675 tiles, one with a dL/dimage and the others
-    without, give that view's gradient.  What differs is the order in which a
+@pytest.mark.parametrize("n,extent,logscale", [(25, 0.3, -1.5), (400, 0.3, -1.5), (400, 0.02, -5.0)])
+def test_backward_of_few_and_of_many_tiles(n, extent, logscale, dtype, rtol):
+    """The backward compositing kernels (eight waves a tile in small grids, in short
+    batches or, where a few lists are far longer than the others, as in the last
+    scene, in long ones; one wave in large grids: over 5120 tiles) form every
+    entry's sums by the same operations in the same order: 8 views of 675 tiles,
+    one with a dL/dimage and the others without, give that view's gradient.  What differs is the order in which a
     Gaussian's tiles are added (64 at a time in a scan, so at most 6 + 12
     roundings), of terms that may cancel to a hundredth."""
-    print(f"case: {n} Gaussians, {dtype}", flush=True)
+    print(f"case: {n} Gaussians, {extent}, {logscale}, {dtype}", flush=True)
     w, h, m = 425, 391, 8
-    th = torch.tensor(synth.dense_scene(n, 44, extent=0.3, logscale_mu=-1.5, logscale_sigma=0.6), device="cuda",
+    th = torch.tensor(synth.dense_scene(n, 44, extent=extent, logscale_mu=logscale, logscale_sigma=0.6), device="cuda",
                       dtype=dtype)
     cams = [synth.look_at((2.5, 0.3, 0.4 + 0.1 * i), (0, 0, 0), (0, 0, 1), w, h, 350.0) for i in range(m)]
     rast = Rasterizer("cuda")
