@@ -664,6 +664,12 @@ __global__ void __launch_bounds__(kOrderTiles) k_order_place(const uint32_t* __r
 // tile's ranking is a chain of rounds), sixteen of four no faster.
 constexpr int kDepthWaves = 8;
 constexpr int kDepthRounds = 64 / kDepthWaves;
+// Few pairs (by their bound, V N) give few such tiles, and a tile's chain of rounds
+// is what a pass waits for: up to 64 Ki pairs tiles of two rounds (1024 keys), up
+// to 1 Mi of four.  A pass (the last one), us, with rounds of 2, 4 and 8: 1.9k
+// pairs 3.9 (4.6), 4.5 (5.2), 5.8 (6.6); 20k 6.8 (7.8), 7.4 (8.9), 8.6 (12.7); 148k
+// pairs of 328k 10.9 (11.1), 9.8 (11.2), 10.2 (14.0).
+inline int depth_rounds(int64_t nv) { return nv <= (1 << 16) ? 2 : (nv <= (1 << 20) ? 4 : kDepthRounds); }
 
 struct BinLayout {
   uint32_t *vis_off, *ka, *va, *kb, *vb, *inst_off, *tka, *tva, *tkb, *tvb, *inst_rec, *ranges, *order;
@@ -709,7 +715,7 @@ static BinLayout bin_layout(void* ws, int n_cams, int64_t n_pidx, int64_t n_tile
   L.order = cv.take<uint32_t>(ntt);
   L.tvis = cv.take<unsigned long long>(2 * ntt);
   L.ctl = cv.take<uint32_t>(kOsCtlLen);
-  L.status = cv.take<unsigned long long>(onesweep_status_count(nv, 4, (int64_t)kWave * kDepthWaves * kDepthRounds));
+  L.status = cv.take<unsigned long long>(onesweep_status_count(nv, 4, (int64_t)kWave * kDepthWaves * depth_rounds(nv)));
   const int64_t nob = ceil_div(ntt, kOrderTiles);
   const bool order_radix = nob > kOrderMaxBlocks;
   L.oka = cv.take<uint32_t>(order_radix ? ntt : 0);
@@ -1079,9 +1085,11 @@ extern "C" tide_status tide_bin_sort(const tide_proj* proj, int32_t tiles_x, int
   //    rectangle's width and its tile count (into vis_off, free once the
   //    compaction has run)
   uint32_t *pfirst, *vrec;
-  onesweep_sort_pairs<kDepthRounds, kDepthWaves>(
-      L.ka, L.va, L.kb, L.vb, nv, 32, false, OsWork{L.ctl, L.status, err}, st, &pfirst, &vrec, &L.totals[0],
-      PairRectOut{L.ka, L.va, L.pwidth, L.vis_off, proj->rect, nv, N, (uint32_t)nt, (uint32_t)tiles_x});
+  auto depth_sort = onesweep_sort_pairs<kDepthRounds, kDepthWaves, PairRectOut>;
+  if (depth_rounds(nv) == 2) depth_sort = onesweep_sort_pairs<2, kDepthWaves, PairRectOut>;
+  if (depth_rounds(nv) == 4) depth_sort = onesweep_sort_pairs<4, kDepthWaves, PairRectOut>;
+  depth_sort(L.ka, L.va, L.kb, L.vb, nv, 32, false, OsWork{L.ctl, L.status, err}, st, &pfirst, &vrec, &L.totals[0],
+             PairRectOut{L.ka, L.va, L.pwidth, L.vis_off, proj->rect, nv, N, (uint32_t)nt, (uint32_t)tiles_x});
   TIDE_LAUNCH_CHECK("depth sort");
   // 3. instance offsets in depth order, closed by inst_off[n_vis] = n_inst;
   //    the block that holds the total also copies the counts and the depth

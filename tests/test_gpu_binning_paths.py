@@ -1,5 +1,6 @@
 """The binning where its small-scene paths end: scans that read their predecessors'
-elements (to 8 blocks of 4096), tile sorts that add the counts up themselves (to
+elements (to 8 blocks of 4096), depth sorts in tiles of 1024 keys (to 65536 pairs)
+and 2048 (to 1048576), tile sorts that add the counts up themselves (to
 512 tiles of 4096 by the workspace) and launch orders without a counting launch
 (to 4 blocks of 256 tiles).  Every list is a whole number: equal, not close."""
 import pytest
@@ -48,6 +49,8 @@ def check(rast, proj, bins, tx, ty):
 @pytest.mark.parametrize("n,views,width,height", [
     (1, 1, 16, 16), (500, 1, 64, 64), (4096, 1, 250, 256), (4097, 1, 257, 256),      # one block, two
     (32768, 1, 300, 200), (32769, 1, 300, 200), (9000, 4, 512, 512),                 # eight blocks, nine, twelve
+    (16384, 4, 200, 200), (20480, 4, 200, 200),                                      # 65536 pairs at most, 81920
+    (262144, 4, 100, 100), (266240, 4, 100, 100),                                    # 1048576, 1064960
     (3000, 1, 512, 512), (3000, 1, 513, 512), (3000, 1, 1040, 1072)])                # 1024 tiles, 1056, 4355
 def test_lists(n, views, width, height, inst_cap):
     print(f"case: {n} Gaussians, {views} x {width}x{height}, room for {inst_cap}", flush=True)
