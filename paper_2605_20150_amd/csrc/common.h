@@ -80,6 +80,7 @@ struct Mth<float> {
   __device__ static float floor(float x) { return floorf(x); }
   __device__ static float log_fast(float x) { return 0.69314718f * __builtin_amdgcn_logf(x); }
   __device__ static float max(float a, float b) { return fmaxf(a, b); }
+  __device__ static float abs(float x) { return fabsf(x); }
   __device__ static float clamp(float x, float lo, float hi) { return __builtin_amdgcn_fmed3f(x, lo, hi); }
   __device__ static float fma(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
 };
@@ -95,6 +96,7 @@ struct Mth<double> {
   __device__ static double floor(double x) { return ::floor(x); }
   __device__ static double log_fast(double x) { return ::log(x); }
   __device__ static double max(double a, double b) { return fmax(a, b); }
+  __device__ static double abs(double x) { return fabs(x); }
   __device__ static double clamp(double x, double lo, double hi) { return fmin(fmax(x, lo), hi); }
   __device__ static double fma(double a, double b, double c) { return __builtin_fma(a, b, c); }
 };

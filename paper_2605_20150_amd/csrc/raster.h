@@ -148,7 +148,8 @@ struct Ex<double> {
 };
 
 // Opacity-weighted Gaussian of one list entry at one pixel, shared by the
-// forward and backward kernels so that both take identical skip decisions.
+// forward and backward kernels: with box_may_take, which never passes over a
+// pixel that these tests accept, both directions take the same entries.
 // A pixel row at +infinity is reached by no entry: the power is -infinity
 // (G = 0) or NaN (both tests fail).
 // The per-entry terms are prepared once per lane column: with the scaled
@@ -180,20 +181,26 @@ __device__ __forceinline__ double alpha_clamped(double araw, bool below) {
 }
 
 // Test of one list entry against a box of W x H pixels whose first centre is
-// (x0 + 0.5, y0 + 0.5), conservative: false only when no pixel centre of the box
-// can take the entry, i.e. when opacity * G < 1/255 at every centre,
-// G = exp(-Q/2), Q = A dx^2 + 2 B dx dy + C dy^2 (the conic is positive
-// definite).  The minimum of Q over the continuous box of the pixel centres
-// bounds it over the centres: 0 if the mean is inside, else the least of the
-// four edge minima (on an edge, Q is a 1-D quadratic minimised at the clamped
-// stationary point).  A slack of 1e-3 (relative and absolute) covers the
-// rounding of this test and of the per-pixel one.
+// (x0 + 0.5, y0 + 0.5), conservative: false only when entry_alpha_tests accepts
+// no pixel centre of the box, as these kernels compute it, for whatever box: the
+// forward and the backward kernels use different ones and must agree.  The
+// least Q = A dx^2 + 2 B dx dy + C dy^2 over the continuous box of the pixel
+// centres bounds it over the centres (G = exp(-Q/2)): 0 if the mean is inside,
+// else the least of the four edge minima (on an edge, Q is a 1-D quadratic
+// minimised at the clamped stationary point; its two curvatures are positive).
+// Rounding, in units of u = 2^-24 (FP64: 2^-53) of the sum S of the three terms'
+// sizes at the box's farthest corner: a pixel's power is off by 5 at most, an
+// edge's least Q by 4 and by 8 for the box's rounded sides; 32 u S are allowed.
+// The terms of a long oblique footprint cancel, so S is far above Q there (a
+// footprint of 3000 px: without S, 20 of 350 000 taken pixels were passed over by
+// one 8 x 8 box or another); for a round one S is Q or so, and nothing changes.
+// A slack of 1e-3 (relative and absolute) covers the exponential and the logarithm.
 // box_prepare forms what does not depend on the box, once per entry: the slopes
 // of the stationary points, -B/A and -B/C, and the bound on Q/2 in the scaled
 // conic's units; box_may_take takes the scaled conic of entry_alpha_tests
 // (Ah = -A k/2, Bh = -B k, Ch = -C k/2), in which -k Q / 2 = Ah dx^2 + Bh dx dy +
-// Ch dy^2.  (Reciprocals within an ulp: a point of the edge that is off by that
-// still bounds Q within the slack.)
+// Ch dy^2.  (Reciprocals within an ulp: Q has no slope at a stationary point, so
+// one that is off by that gives the same least Q.)
 template <typename T>
 __device__ __forceinline__ void box_prepare(T A, T B, T C, T op, T& ka, T& kc, T& lim) {
   ka = -B * Mth<T>::rcp_fast(A);
@@ -208,7 +215,11 @@ __device__ __forceinline__ bool box_may_take(T u, T v, T Ah, T Bh, T Ch, T ka, T
   auto p = [&](T dx, T dy) { return dx * (Ah * dx + Bh * dy) + Ch * dy * dy; };
   const T e0 = p(xa, cl(kc * xa, ya, yb)), e1 = p(xb, cl(kc * xb, ya, yb));
   const T e2 = p(cl(ka * ya, xa, xb), ya), e3 = p(cl(ka * yb, xa, xb), yb);
-  const T best = Mth<T>::max(Mth<T>::max(e0, e1), Mth<T>::max(e2, e3));
+  auto abs = [](T x) { return Mth<T>::abs(x); };
+  const T fx = Mth<T>::max(abs(xa), abs(xb)), fy = Mth<T>::max(abs(ya), abs(yb));
+  const T far = (abs(Ah) * fx + abs(Bh) * fy) * fx + abs(Ch) * fy * fy;   // S
+  const T eps = sizeof(T) == 4 ? (T)0x1p-19 : (T)0x1p-48;
+  const T best = Mth<T>::fma(eps, far, Mth<T>::max(Mth<T>::max(e0, e1), Mth<T>::max(e2, e3)));
   const bool inside = xa <= (T)0 && xb >= (T)0 && ya <= (T)0 && yb >= (T)0;
   return inside ? lim <= (T)0 : !(best < lim);
 }

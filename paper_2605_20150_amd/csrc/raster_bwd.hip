@@ -147,8 +147,7 @@ __global__ void __launch_bounds__(64) k_render_bwd(const uint32_t* __restrict__ 
       s_o[lane] = q[5]; s_r[lane] = q[6]; s_g[lane] = q[7]; s_b[lane] = q[8];
       may = tile_may_take<T>(q[0], q[1], q[2], q[3], q[4], q[5], tx, ty);
     }
-    // entries some pixel centre of the tile may take (the forward's test),
-    // walked from the back; hit: the entries some pixel took
+    // entries some pixel centre of the tile may take, walked from the back; hit: the entries some pixel took
     uint64_t rest = __ballot(may), hit = 0;
     __syncthreads();
     while (rest != 0) {
