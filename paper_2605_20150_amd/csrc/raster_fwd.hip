@@ -29,7 +29,16 @@ CamSet<T> make_camset(const tide_camera* cams, int n) {
     d.limx = (T)(1.3 * 0.5 * c.width / c.fx);
     d.limy = (T)(1.3 * 0.5 * c.height / c.fy);
     const double limx = d.limx, limy = d.limy;
-    d.reach = 3.03 * std::sqrt(c.fx * c.fx * (1 + limx * limx) + c.fy * c.fy * (1 + limy * limy));
+    // |R| <= sqrt of the largest absolute row sum of R R^T: 1 for a rotation, but
+    // a camera may scale
+    double rr = 1;
+    for (int a = 0; a < 3; ++a) {
+      double row = 0;
+      for (int b = 0; b < 3; ++b)
+        row += std::fabs(c.R[3 * a] * c.R[3 * b] + c.R[3 * a + 1] * c.R[3 * b + 1] + c.R[3 * a + 2] * c.R[3 * b + 2]);
+      rr = row > rr ? row : rr;
+    }
+    d.reach = 3.03 * std::sqrt(rr * (c.fx * c.fx * (1 + limx * limx) + c.fy * c.fy * (1 + limy * limy)));
     for (int k = 0; k < 3; ++k)
       d.pos[k] = (T)(-(c.R[k] * c.t[0] + c.R[3 + k] * c.t[1] + c.R[6 + k] * c.t[2]));
     d.W = c.width; d.H = c.height;
@@ -70,11 +79,12 @@ __device__ inline double cam_depth(const double* Rd, const double* td, double m0
 }
 // Conservative test of a mean at camera depth pz against the image: false only
 // when the footprint's tile rectangle is surely empty.  The radius is 3 sqrt of
-// the largest eigenvalue of J S J^T + 0.3 I, at most 3 (|J|_F smax + sqrt 0.3) with
-// |J|_F pz <= sqrt(fx^2 (1 + limx^2) + fy^2 (1 + limy^2)) and smax the largest
-// scale; one per cent and 17 pixels (the round up to a whole radius and a tile)
-// cover the rounding of both sides.  Everything is multiplied by the depth: no
-// division.  NaN and infinite bounds pass.
+// the largest eigenvalue of J R S R^T J^T + 0.3 I, at most 3 (|J|_F |R| smax +
+// sqrt 0.3) with |J|_F pz <= sqrt(fx^2 (1 + limx^2) + fy^2 (1 + limy^2)), |R| the
+// norm of the camera's R (no rotation need be) and smax the largest scale; one
+// per cent and 17 pixels (the round up to a whole radius and a tile) cover the
+// rounding of both sides.  Everything is multiplied by the depth: no division.
+// NaN and infinite bounds pass.
 template <typename T>
 __device__ __forceinline__ bool may_meet_image(const DevCam<T>& cm, double m0, double m1, double m2, double pz, T smax) {
   const double x = cm.fxd * (cm.Rd[0] * m0 + cm.Rd[1] * m1 + cm.Rd[2] * m2 + cm.td[0]) + cm.cxd * pz;

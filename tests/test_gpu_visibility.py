@@ -31,3 +31,25 @@ def test_kept_pairs(width, height, focal, shift):
     got = proj.tiles_touched.view(len(cams), -1)[:, :n].cpu().numpy()
     assert 0.05 < (want > 0).mean() < 0.95
     assert np.array_equal(got, want)
+
+
+@pytest.mark.parametrize("scale", [(3.0, 3.0, 3.0), (0.2, 0.2, 0.2), (1.0, 6.0, 1.0), (4.0, 0.5, 2.0)])
+def test_kept_pairs_of_a_camera_that_scales(scale):
+    """p_cam = R p_world + t with an R that is no rotation: the world's axes scaled."""
+    print(f"case: axes scaled by {scale}", flush=True)
+    n = 4000
+    rng = np.random.Generator(np.random.PCG64(53))
+    th = synth.dense_scene(n, 54).astype(np.float64)
+    th[:, 0:3] = rng.uniform(-1, 1, size=(n, 3)) * np.exp(rng.uniform(-2, 3, size=(n, 1)))
+    th[:, 3:6] = rng.uniform(-4, 1, size=(n, 1)) + rng.uniform(-1, 1, size=(n, 3))
+    cams = [synth.look_at(eye, (0, 0, 0), (0, 0, 1), 70, 41, 60.0) for eye in ((2.5, 0.3, 0.4), (-20.0, 5.0, 3.0))]
+    for c in cams:
+        c.R = np.asarray(c.R, np.float64).reshape(3, 3) @ np.diag(scale)
+        c.t = np.asarray(c.t, np.float64) * max(scale)
+    p = oracle.project(th, synth.cams_array(cams))
+    want = np.where(p["keep"], p["tiles_touched"], 0)
+    rast = Rasterizer("cuda")
+    proj = rast.preprocess(Pool.from_dense(torch.tensor(th, device="cuda"), 500), cams)
+    got = proj.tiles_touched.view(len(cams), -1)[:, :n].cpu().numpy()
+    assert 0.05 < (want > 0).mean() < 0.95
+    assert np.array_equal(got, want)
