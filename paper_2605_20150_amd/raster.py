@@ -16,6 +16,7 @@ from dataclasses import dataclass
 import numpy as np
 import torch
 from torch.autograd import forward_ad
+from torch.utils._device import DeviceContext
 
 from . import _lib as L
 
@@ -35,14 +36,23 @@ def _dtype_code(dt: torch.dtype) -> int:
     raise TypeError(f"unsupported dtype {dt}")
 
 
+def _watched(t: torch.Tensor) -> bool:
+    """Something would see torch's operations on t, or act on them: autograd,
+    forward-mode differentiation, a transform (vmap, functionalize), a tracer
+    (jit.trace, make_fx, compile) or a mode over all operations."""
+    return bool(t.requires_grad or t.is_neg() or forward_ad._current_level >= 0
+                or torch._C._functorch.is_functorch_wrapped_tensor(t) or torch._C._len_torch_dispatch_stack()
+                or any(not isinstance(torch._C._get_function_stack_at(k), DeviceContext)
+                       for k in range(torch._C._len_torch_function_stack()))
+                or torch.jit.is_tracing() or torch.compiler.is_compiling())
+
+
 def _plain(t: torch.Tensor) -> bool:
     """A tensor of values on the current GPU that a kernel may read in torch's
-    place: float32 or float64, nothing recorded, traced, batched or carrying a
-    tangent."""
+    place: float32 or float64, and nothing watches."""
     return (type(t) in (torch.Tensor, torch.nn.Parameter) and t.is_cuda
             and t.device.index == torch.cuda.current_device() and t.dtype in (torch.float32, torch.float64)
-            and not t.requires_grad and not torch._C._functorch.is_functorch_wrapped_tensor(t)
-            and forward_ad._current_level < 0 and not torch.compiler.is_compiling())
+            and not _watched(t))
 
 
 class Buffers:
@@ -102,8 +112,8 @@ class Pool:
         N = theta.shape[0]
         K = max(1, math.ceil(N / block_rows))
         dev = theta.device
-        if (theta.dim() == 2 and theta.shape[1] == D and 0 < N and 0 <= extra_slots and 0 < block_rows
-                and _plain(theta) and theta.is_contiguous()):
+        if (_plain(theta) and theta.dim() == 2 and theta.shape[1] == D and 0 < N and 0 <= extra_slots
+                and 0 < block_rows and theta.is_contiguous()):
             # one launch in place of fills, copies and a transpose, and no wait for
             # the slot tables' way from host memory
             S = K + int(extra_slots)
@@ -366,7 +376,7 @@ class Rasterizer:
 def dense_grad(proj: Proj, grad: torch.Tensor, n: int) -> torch.Tensor:
     """Compact [59][n_active] gradient -> dense (n, 59) for an all-resident
     pool whose pidx equals the global row id."""
-    if (0 < n <= proj.n_pidx <= grad.shape[-1] and _plain(grad) and grad.dim() == 2 and grad.shape[0] == D
+    if (_plain(grad) and 0 < n <= proj.n_pidx <= grad.shape[-1] and grad.dim() == 2 and grad.shape[0] == D
             and grad.stride(1) == 1 and grad.stride(0) >= grad.shape[1] and _dtype_code(grad.dtype) == proj.dtype
             and proj.active.shape[0] == proj.n_pidx):
         # one launch, and the host does not wait for the active rows' number

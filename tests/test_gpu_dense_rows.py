@@ -45,3 +45,14 @@ def test_dense_gradient(n, dtype):
     # recorded by autograd: the general path, differentiable
     gr = g.clone().requires_grad_(True)
     assert dense_grad(proj, gr, n).requires_grad
+
+
+def test_traced_programs_see_the_operations():
+    """A program recorded on one table runs on another: by jit.trace and by make_fx,
+    both of which hand over tensors of values."""
+    from torch.fx.experimental.proxy_tensor import make_fx
+    a, b = (torch.randn(10, D, generator=torch.Generator().manual_seed(s)).cuda() for s in (1, 2))
+    want = Pool.from_dense(b, 4).params
+    for record in (lambda f, x: torch.jit.trace(f, x, check_trace=False), lambda f, x: make_fx(f)(x)):
+        print("case: a recorded program", flush=True)
+        assert torch.equal(record(lambda t: Pool.from_dense(t, 4).params, a)(b), want)
