@@ -16,9 +16,13 @@ from dataclasses import dataclass
 import numpy as np
 import torch
 from torch.autograd import forward_ad
-from torch.utils._device import DeviceContext
 
 from . import _lib as L
+
+try:
+    from torch.utils._device import DeviceContext
+except ImportError:
+    DeviceContext = ()
 
 D = 59
 TILE = 16
@@ -39,12 +43,16 @@ def _dtype_code(dt: torch.dtype) -> int:
 def _watched(t: torch.Tensor) -> bool:
     """Something would see torch's operations on t, or act on them: autograd,
     forward-mode differentiation, a transform (vmap, functionalize), a tracer
-    (jit.trace, make_fx, compile) or a mode over all operations."""
-    return bool(t.requires_grad or t.is_neg() or forward_ad._current_level >= 0
-                or torch._C._functorch.is_functorch_wrapped_tensor(t) or torch._C._len_torch_dispatch_stack()
-                or any(not isinstance(torch._C._get_function_stack_at(k), DeviceContext)
-                       for k in range(torch._C._len_torch_function_stack()))
-                or torch.jit.is_tracing() or torch.compiler.is_compiling())
+    (jit.trace, make_fx, compile) or a mode over all operations.  Also when this
+    torch lacks the means to tell."""
+    try:
+        return bool(t.requires_grad or t.is_neg() or forward_ad._current_level >= 0
+                    or torch._C._functorch.is_functorch_wrapped_tensor(t) or torch._C._len_torch_dispatch_stack()
+                    or any(not isinstance(torch._C._get_function_stack_at(k), DeviceContext)
+                           for k in range(torch._C._len_torch_function_stack()))
+                    or torch.jit.is_tracing() or torch.compiler.is_compiling())
+    except AttributeError:
+        return True
 
 
 def _plain(t: torch.Tensor) -> bool:

@@ -1,5 +1,5 @@
 """When the one-launch layout kernels may stand in for torch's operations: never
-while something watches the operations."""
+while something watches the operations, and never when torch cannot say."""
 import pytest
 import torch
 from torch.autograd import forward_ad
@@ -55,3 +55,11 @@ def device(f):
 ])
 def test_watched_tensors(name, run, want):
     assert seen(run) is want
+
+
+@pytest.mark.parametrize("owner,attr", [(torch._C, "_functorch"), (forward_ad, "_current_level"),
+                                        (torch._C, "_len_torch_dispatch_stack"), (torch.compiler, "is_compiling")])
+def test_a_torch_that_cannot_say_takes_the_general_path(monkeypatch, owner, attr):
+    monkeypatch.delattr(owner, attr)
+    assert raster._watched(torch.zeros(3)) is True
+    assert raster._plain(torch.zeros(3)) is False
