@@ -236,15 +236,23 @@ __global__ void __launch_bounds__(kScanThreads) k_scan_down(In in, int64_t n_max
   // exclusive scan of the 256 thread sums
   const uint32_t inc = wave_incl_scan(s);
   __shared__ uint32_t wtot[kScanThreads / kWave];
+  __shared__ unsigned long long wall[kFrom == kSelf ? kScanThreads / kWave : 1];   // the total needs more than 32 bits
   const int w = threadIdx.x / kWave;
   if (__lane_id() == kWave - 1) wtot[w] = inc;
+  if (kFrom == kSelf && blockIdx.x == nb - 1) {
+    unsigned long long a = 0;
+#pragma unroll
+    for (int k = 0; k < kScanItems; ++k) a += v[k];
+    a = wave_sum(a);
+    if (__lane_id() == 0) wall[kFrom == kSelf ? w : 0] = a;
+  }
   __syncthreads();
   uint32_t wpre = 0;
   for (int q = 0; q < w; ++q) wpre += wtot[q];
   uint32_t run = (uint32_t)bp + wpre + inc - s;
   if (kFrom == kSelf && blockIdx.x == nb - 1 && threadIdx.x == 0) {
     unsigned long long t = bp;
-    for (int q = 0; q < kScanThreads / kWave; ++q) t += wtot[q];
+    for (int q = 0; q < kScanThreads / kWave; ++q) t += wall[kFrom == kSelf ? q : 0];
     *total = t;
     write_tail(tail, t, n);
   }

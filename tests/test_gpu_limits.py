@@ -1,0 +1,37 @@
+"""Sizes at the ends of what the entry points accept."""
+import ctypes as C
+
+import pytest
+import torch
+
+from paper_2605_20150_amd import _lib as L
+from paper_2605_20150_amd.raster import Proj, Rasterizer, _stream
+
+pytestmark = pytest.mark.gpu
+
+
+def wide_pairs(n, side):
+    """n pairs that cover a whole grid of side x side tiles each."""
+    dev = "cuda"
+    return Proj(rec=torch.zeros(12 * n, device=dev), depth=torch.arange(1, n + 1, device=dev, dtype=torch.float32),
+                rect=torch.tensor([0, side | side << 16] * n, device=dev, dtype=torch.int32),
+                tiles_touched=torch.full((n,), side * side, device=dev, dtype=torch.int32),
+                active=torch.ones(n, device=dev, dtype=torch.int32),
+                act_idx=torch.arange(n, device=dev, dtype=torch.int32),
+                n_active=torch.tensor([n], device=dev, dtype=torch.int32), n_cams=1, n_pidx=n, dtype=L.TIDE_F32)
+
+
+@pytest.mark.parametrize("n", [255, 256, 300, 4500])
+def test_the_instance_count_is_not_cut_to_32_bits(n):
+    """Pairs of 2^24 tiles, counted by each of the scans (in one block and in two);
+    from 2^32 - 1 instances on the call is refused."""
+    print(f"case: {n} pairs x 2^24 tiles, little room", flush=True)
+    side = 4096
+    proj = wide_pairs(n, side)
+    rast = Rasterizer("cuda")
+    ws = rast.buf.get("bin_ws", rast.lib.tide_bin_sort_ws_bytes(1, n, side, side, 1 << 16))
+    bins = L.tide_bins()
+    code = rast.lib.tide_bin_sort(C.byref(proj.c()), side, side, C.c_void_p(ws.data_ptr()), ws.numel(),
+                                  C.byref(bins), C.c_void_p(_stream()))
+    assert bins.n_inst == n * side * side
+    assert code == (L.TIDE_ECAPACITY if n < 256 else L.TIDE_EINVAL)
