@@ -438,7 +438,8 @@ __global__ void __launch_bounds__(64) k_emit(const uint32_t* __restrict__ first,
   const int lane = threadIdx.x;
   for (int64_t i = (int64_t)blockIdx.x * kWave + lane; i < n_zero; i += (int64_t)gridDim.x * kWave) zero[i] = 0u;
   // pair and instance indices fit 32 bits (a larger count is refused after the
-  // fact; the clamp keeps this kernel in bounds then)
+  // fact; the clamp keeps this kernel in bounds then, and k_ranges passes over
+  // what it wrote)
   const uint32_t n_vis = (uint32_t)dev_count(nv_max, d_nvis);
   const int64_t n = dev_count(cap < 0xffffffffll ? cap : 0xffffffffll, d_ninst);
   if (n_vis == 0) return;
@@ -513,11 +514,12 @@ __global__ void __launch_bounds__(64) k_emit(const uint32_t* __restrict__ first,
 // load when kVec: the keys are 16-byte aligned) and compares each with its
 // neighbours; ~0u stands in past either end (keys are below 2^31).
 // After a failed depth sort (*err set) the ranges stay empty, so the
-// compositing reads no entry.
+// compositing reads no entry; and past 32-bit instances (the call is refused
+// then), as the offsets wrap and the emission leaves keys unwritten.
 template <bool kVec>
 __global__ void k_ranges(const uint32_t* __restrict__ key, int64_t n_max, const unsigned long long* __restrict__ d_n,
                          uint32_t* __restrict__ ranges, const uint32_t* __restrict__ err) {
-  if (*err) return;
+  if (*err || *d_n >= 0xffffffffull) return;
   const int64_t n = dev_count(n_max, d_n);
   const int64_t stride = 4 * (int64_t)gridDim.x * blockDim.x;
   for (int64_t j0 = 4 * ((int64_t)blockIdx.x * blockDim.x + threadIdx.x); j0 < n; j0 += stride) {

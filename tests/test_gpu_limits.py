@@ -10,6 +10,12 @@ from paper_2605_20150_amd.raster import Proj, Rasterizer, _stream
 pytestmark = pytest.mark.gpu
 
 
+def room(gigabytes):
+    torch.cuda.empty_cache()
+    if torch.cuda.mem_get_info()[0] < gigabytes * 1e9:
+        pytest.skip(f"needs {gigabytes} GB of device memory")
+
+
 def wide_pairs(n, side):
     """n pairs that cover a whole grid of side x side tiles each."""
     dev = "cuda"
@@ -35,3 +41,22 @@ def test_the_instance_count_is_not_cut_to_32_bits(n):
                                   C.byref(bins), C.c_void_p(_stream()))
     assert bins.n_inst == n * side * side
     assert code == (L.TIDE_ECAPACITY if n < 256 else L.TIDE_EINVAL)
+
+
+def test_the_last_instances_below_32_bits():
+    """300 pairs of 2^24 tiles and a workspace that holds nearly 2^32 instances, so
+    that the last ones are emitted where the 32-bit offsets wrap: refused, and
+    whatever the workspace held before (here keys far beyond the grid), nothing is
+    written outside of it."""
+    print("case: 300 pairs x 2^24 tiles, room for nearly 2^32 instances", flush=True)
+    room(150)
+    side = 4096
+    proj = wide_pairs(300, side)
+    rast = Rasterizer("cuda")
+    rast.inst_cap = (1 << 32) - (1 << 20)
+    rast.buf.get("bin_ws", rast.lib.tide_bin_sort_ws_bytes(1, 300, side, side, rast.inst_cap)).fill_(255)
+    with pytest.raises(L.TideError, match="32-bit"):
+        rast.bin_sort(proj, side, side)
+    torch.cuda.synchronize()
+    del rast
+    torch.cuda.empty_cache()
