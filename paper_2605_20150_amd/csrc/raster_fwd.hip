@@ -773,7 +773,7 @@ __global__ void __launch_bounds__(256) k_render_fwd(const uint32_t* __restrict__
                                                     int32_t Tx, int32_t Ty, int32_t W, int32_t H, T bg0, T bg1, T bg2,
                                                     T* __restrict__ image, T* __restrict__ tfin,
                                                     uint32_t* __restrict__ last_out,
-                                                    unsigned long long* __restrict__ tile_visits) {
+                                                    unsigned long long* __restrict__ tile_visits, uint32_t n_tiles) {
   constexpr int kQ = kTile / 2;
   const int nt = Tx * Ty;
   const int g = (int)order[blockIdx.x];
@@ -920,7 +920,7 @@ __global__ void __launch_bounds__(256) k_render_fwd(const uint32_t* __restrict__
   __syncthreads();
   if (tid == 0) {
     tile_visits[g] = s_vis[0] + s_vis[1] + s_vis[2] + s_vis[3];
-    tile_visits[gridDim.x + g] = s_back[0] + s_back[1] + s_back[2] + s_back[3];
+    tile_visits[n_tiles + g] = s_back[0] + s_back[1] + s_back[2] + s_back[3];
   }
 }
 
@@ -1216,16 +1216,22 @@ extern "C" tide_status tide_render_fwd(const tide_proj* proj, const tide_bins* b
                      (fr->height + kTile - 1) / kTile == bins->tiles_y,
                  "frame size does not match the tile grid");
   hipStream_t st = (hipStream_t)stream;
-  const uint32_t grid = (uint32_t)(bins->n_cams * bins->tiles_x * bins->tiles_y);
+  const uint32_t n_tiles = (uint32_t)(bins->n_cams * bins->tiles_x * bins->tiles_y);
+  // a launch holds fewer than 2^32 threads; the tiles after them go to another one
+  auto render = [&](auto kernel, auto* rec, auto* image, auto* tfin, auto b0, auto b1, auto b2) {
+    constexpr uint32_t kMost = 1u << 23;
+    for (uint32_t t = 0; t < n_tiles; t += kMost)
+      hipLaunchKernelGGL(kernel, dim3(n_tiles - t < kMost ? n_tiles - t : kMost), dim3(256), 0, st,
+                         bins->tile_order + t, bins->ranges, bins->inst_e, bins->inst_rec, rec, bins->tiles_x,
+                         bins->tiles_y, fr->width, fr->height, b0, b1, b2, image, tfin, fr->last, bins->tile_visits,
+                         n_tiles);
+  };
   if (proj->dtype == TIDE_F32)
-    TIDE_TIMED("render_fwd", st, hipLaunchKernelGGL(k_render_fwd<float>, dim3(grid), dim3(256), 0, st, bins->tile_order, bins->ranges, bins->inst_e, bins->inst_rec,
-                       (const float*)proj->rec, bins->tiles_x, bins->tiles_y, fr->width, fr->height, bg[0], bg[1],
-                       bg[2], (float*)fr->image, (float*)fr->t_final, fr->last, bins->tile_visits));
+    TIDE_TIMED("render_fwd", st, render(k_render_fwd<float>, (const float*)proj->rec, (float*)fr->image,
+                                        (float*)fr->t_final, bg[0], bg[1], bg[2]));
   else
-    TIDE_TIMED("render_fwd", st, hipLaunchKernelGGL(k_render_fwd<double>, dim3(grid), dim3(256), 0, st, bins->tile_order, bins->ranges, bins->inst_e,
-                       bins->inst_rec, (const double*)proj->rec, bins->tiles_x, bins->tiles_y, fr->width,
-                       fr->height, (double)bg[0], (double)bg[1], (double)bg[2], (double*)fr->image,
-                       (double*)fr->t_final, fr->last, bins->tile_visits));
+    TIDE_TIMED("render_fwd", st, render(k_render_fwd<double>, (const double*)proj->rec, (double*)fr->image,
+                                        (double*)fr->t_final, (double)bg[0], (double)bg[1], (double)bg[2]));
   TIDE_LAUNCH_CHECK("k_render_fwd");
   hipLaunchKernelGGL(k_sum_visits, dim3((uint32_t)(2 * bins->n_cams * kVisitParts)), dim3(256), 0, st, bins->tile_visits,
                      (int64_t)bins->tiles_x * bins->tiles_y, bins->n_cams, fr->visits);

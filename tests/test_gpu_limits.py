@@ -5,7 +5,8 @@ import pytest
 import torch
 
 from paper_2605_20150_amd import _lib as L
-from paper_2605_20150_amd.raster import Proj, Rasterizer, _stream
+from paper_2605_20150_amd import synth
+from paper_2605_20150_amd.raster import Pool, Proj, Rasterizer, _stream
 
 pytestmark = pytest.mark.gpu
 
@@ -59,4 +60,32 @@ def test_the_last_instances_below_32_bits():
         rast.bin_sort(proj, side, side)
     torch.cuda.synchronize()
     del rast
+    torch.cuda.empty_cache()
+
+
+def test_an_image_of_more_than_2_to_the_24_tiles():
+    """Eight views of 33 x 65535 tiles, one Gaussian near the lower end of each: the
+    last rows are those of a small view moved along, the others the background."""
+    print("case: 8 views of 513x1048560", flush=True)
+    room(110)
+    w, h, low, bg = 513, 16 * 65535, 48, (0.25, 0.5, 0.75)
+    th = synth.dense_scene(1, 3, extent=0.0, logscale_mu=-1.5, logscale_sigma=0.1)
+    pool = Pool.from_dense(torch.tensor(th, device="cuda", dtype=torch.float32), 1)
+
+    def views(height):
+        return [synth.look_at((3.0, 0, 0), (0, 0, 0), (0, 0, 1), w, height, 100.0, cx=500.0 - i, cy=height - 20.0)
+                for i in range(8)]
+
+    small = Rasterizer("cuda").forward(pool, views(low), bg)[2]
+    assert (small.last > 0).any()
+    rast = Rasterizer("cuda")
+    fr = rast.forward(pool, views(h), bg)[2]
+    for name in ("image", "t_final", "last"):
+        assert torch.equal(getattr(fr, name)[..., -low:, :], getattr(small, name)), name
+    for v in range(8):
+        for c in range(3):
+            assert bool((fr.image[v, c, :-low] == bg[c]).all())
+        assert bool((fr.t_final[v, :-low] == 1).all()) and not bool(fr.last[v, :-low].any())
+    assert torch.equal(fr.visits[1], small.visits[1])
+    del fr, rast
     torch.cuda.empty_cache()
