@@ -8,6 +8,7 @@
 // the newest input row.  LDS carries only the horizontal exchange (two values
 // per pixel in the forward, three in the backward), and the next input row is
 // in flight while the current one is processed.
+#include <algorithm>
 #include <cmath>
 
 #include "common.h"
@@ -33,15 +34,19 @@ constexpr int kMaxTurnsFwd = 10, kMaxTurnsBwd = 8;
 __host__ __device__ constexpr int rows_of(int turns) { return kTaps * turns - 2 * kHalo; }
 struct Turns {
   int fwd, bwd;
+  int64_t fwd_waves_max;   // of this and all smaller frames: the room of the waves' partial sums
   Turns(int32_t n_views, int32_t height, int32_t width, int32_t dtype) {
     const int64_t strips = 3 * (int64_t)n_views * ceil_div(width, kWave), simds = 4 * 256;
-    auto fewest = [&](int most, int64_t waves) {
+    auto waves = [&](int turns) { return strips * ceil_div(height, rows_of(turns)); };
+    auto fewest = [&](int most, int64_t at_a_time) {
       int t = 2;
-      while (t < most && strips * ceil_div(height, rows_of(t)) > waves) ++t;
+      while (t < most && waves(t) > at_a_time) ++t;
       return t;
     };
-    fwd = fewest(kMaxTurnsFwd, simds * (dtype == TIDE_F64 ? 2 : 4));
+    const int64_t fwd_at_a_time = simds * (dtype == TIDE_F64 ? 2 : 4);
+    fwd = fewest(kMaxTurnsFwd, fwd_at_a_time);
     bwd = fewest(kMaxTurnsBwd, simds * (dtype == TIDE_F64 ? 3 : 5));
+    fwd_waves_max = std::min(waves(2), std::max(fwd_at_a_time, waves(kMaxTurnsFwd)));
   }
 };
 
@@ -248,8 +253,7 @@ using namespace tide;
 extern "C" size_t tide_loss_ws_bytes(int32_t n_views, int32_t height, int32_t width, int32_t dtype) {
   const size_t es = dtype == TIDE_F64 ? 8 : 4;
   const size_t planes = (size_t)n_views * 3;
-  const int rows = rows_of(Turns(n_views, height, width, dtype).fwd);
-  const size_t nblk = planes * ceil_div(width, kWave) * ceil_div(height, rows);
+  const size_t nblk = (size_t)Turns(n_views, height, width, dtype).fwd_waves_max;
   return align_up(3 * planes * (size_t)height * width * es) + align_up(2 * nblk * sizeof(double)) + 256;
 }
 
