@@ -1,6 +1,7 @@
 // Forward half of the rasterizer: preprocessing (projection, culling, EWA
 // footprint, tile rectangle, SH colour), tile binning with the two-level
 // depth/tile radix sort, and front-to-back compositing.
+#include <algorithm>
 #include <cmath>
 #include <cstring>
 #include <mutex>
@@ -683,6 +684,15 @@ constexpr int kDepthRounds = 64 / kDepthWaves;
 // pairs of 328k 10.9 (11.1), 9.8 (11.2), 10.2 (14.0).
 inline int depth_rounds(int64_t nv) { return nv <= (1 << 16) ? 2 : (nv <= (1 << 20) ? 4 : kDepthRounds); }
 
+// Room for the look-back words of nv pairs and of any fewer (whose tiles may be
+// shorter, and so more), that a workspace may serve smaller scenes.
+inline size_t depth_status_count(int64_t nv) {
+  size_t most = 0;
+  for (int64_t n : {nv, std::min<int64_t>(nv, 1 << 20), std::min<int64_t>(nv, 1 << 16)})
+    most = std::max(most, onesweep_status_count(n, 4, (int64_t)kWave * kDepthWaves * depth_rounds(n)));
+  return most;
+}
+
 struct BinLayout {
   uint32_t *vis_off, *ka, *va, *kb, *vb, *inst_off, *tka, *tva, *tkb, *tvb, *inst_rec, *ranges, *order;
   uint32_t *oka, *ova, *okb, *ovb;   // launch-order radix sort (grids beyond kOrderMaxBlocks blocks)
@@ -727,7 +737,7 @@ static BinLayout bin_layout(void* ws, int n_cams, int64_t n_pidx, int64_t n_tile
   L.order = cv.take<uint32_t>(ntt);
   L.tvis = cv.take<unsigned long long>(2 * ntt);
   L.ctl = cv.take<uint32_t>(kOsCtlLen);
-  L.status = cv.take<unsigned long long>(onesweep_status_count(nv, 4, (int64_t)kWave * kDepthWaves * depth_rounds(nv)));
+  L.status = cv.take<unsigned long long>(depth_status_count(nv));
   const int64_t nob = ceil_div(ntt, kOrderTiles);
   const bool order_radix = nob > kOrderMaxBlocks;
   L.oka = cv.take<uint32_t>(order_radix ? ntt : 0);

@@ -19,3 +19,20 @@ def test_loss(views, width, dtype):
     assert grows(lib.tide_loss_ws_bytes(views, h, width, dtype) for h in range(1, 20000))
     assert grows(lib.tide_loss_ws_bytes(v, 1080, width, dtype) for v in range(1, 100))
     assert grows(lib.tide_loss_ws_bytes(views, 64, w, dtype) for w in range(1, 20000))
+
+
+@pytest.mark.parametrize("line", [1 << 12, 1 << 15, 1 << 16, 1 << 20, 1 << 22])
+def test_binning(line):
+    lib = L.load()
+    for cap in (0, 1 << 16):
+        for v in (1, 4):
+            assert grows(lib.tide_bin_sort_ws_bytes(v, n, 19, 25, cap) for n in range(line // v - 300, line // v + 300))
+    assert grows(lib.tide_bin_sort_ws_bytes(2, 1000, 19, 25, c) for c in range(line - 300, line + 300))
+    assert grows(lib.tide_bin_sort_ws_bytes(1, 1000, x, 64, 1 << 16) for x in range(1, 3000))
+
+
+def test_predictor():
+    lib, mlp = L.load(), L.tide_mlp()
+    mlp.n_layers = 2
+    mlp.dims[0], mlp.dims[1], mlp.dims[2] = 16, 136, 8224
+    assert grows(lib.tide_mlp_ws_bytes(mlp, b) for b in range(1, 600))
