@@ -591,11 +591,16 @@ __device__ __forceinline__ void seg_step(int p, T (&v)[kG2]) {
 // and 64 of them in a row cost one load; a pair without a taken one gets no sum
 // (its gradients are zero), and the others are marked in g2d_on (one byte per
 // record, zero on entry unless mark_all, which writes every visible pair's).
-constexpr int64_t kReduceMin = kWave, kReduceMax = 2048;
+constexpr int64_t kReduceMin = kWave, kReduceMax = 2048, kReduceWaves = 8192;   // the waves fill the chip
 constexpr int64_t kWholeTiles = 1024;
 inline int64_t reduce_piece(int64_t n_inst) {
-  const int64_t p = ceil_div(ceil_div(n_inst, 8192), kWave) * kWave;   // 8192 waves fill the chip
+  const int64_t p = ceil_div(ceil_div(n_inst, kReduceWaves), kWave) * kWave;
   return p < kReduceMin ? kReduceMin : (p > kReduceMax ? kReduceMax : p);
+}
+// The most pieces of n_inst instances or fewer.
+inline int64_t reduce_pieces_max(int64_t n_inst) {
+  const int64_t few = ceil_div(n_inst, kReduceMin), many = ceil_div(n_inst, kReduceMax);
+  return few < kReduceWaves ? few : (many > kReduceWaves ? many : kReduceWaves);
 }
 
 template <typename T, bool kWhole>
@@ -1143,12 +1148,14 @@ struct BwdWs {
     const int64_t n = bins->n_inst > 0 ? bins->n_inst : 1;
     piece = reduce_piece(n);
     pieces = ceil_div(n, piece);
+    // a workspace serves smaller scenes too, which may have more pieces
+    const int64_t room = reduce_pieces_max(n);
     Carver cv(base);
     partial = cv.take<T>((size_t)n * kG2);
     g2d = cv.take<T>((size_t)kG2 * bins->n_cams * bins->n_pidx);
     head = cv.take<T>((size_t)kG2 * ceil_div(n, kWave));
-    tail = cv.take<T>((size_t)kG2 * pieces);
-    tail_pair = cv.take<int64_t>(pieces);
+    tail = cv.take<T>((size_t)kG2 * room);
+    tail_pair = cv.take<int64_t>(room);
     const int64_t nr = (int64_t)bins->n_cams * bins->n_pidx;
     taken = cv.take<uint8_t>(n);
     g2d_on = cv.take<uint8_t>(nr);

@@ -31,6 +31,19 @@ def test_binning(line):
     assert grows(lib.tide_bin_sort_ws_bytes(1, 1000, x, 64, 1 << 16) for x in range(1, 3000))
 
 
+@pytest.mark.parametrize("dtype", [L.TIDE_F32, L.TIDE_F64])
+@pytest.mark.parametrize("line", [64, 1 << 13, 1 << 17, 1 << 19, 1 << 20, 1 << 24, (1 << 24) + (1 << 19)])
+def test_backward(line, dtype):
+    lib, bins = L.load(), L.tide_bins()
+    bins.n_cams, bins.n_pidx, bins.tiles_x, bins.tiles_y = 2, 1000, 19, 25
+
+    def size(n):
+        bins.n_inst = n
+        return lib.tide_render_bwd_ws_bytes(bins, dtype)
+
+    assert grows(size(n) for n in range(max(line - 300, 0), line + 300))
+
+
 def test_predictor():
     lib, mlp = L.load(), L.tide_mlp()
     mlp.n_layers = 2
