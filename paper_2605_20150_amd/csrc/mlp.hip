@@ -678,6 +678,9 @@ constexpr int kLossBlocks = 1024;
 // the logarithm and the double-precision sum bound it: 256 x 65536 (134 MB)
 // 72 us, 86 us with one output per thread and an index division each.
 constexpr int kBcePiece = 1024;
+// The logits are the caller's, aligned to their element: moved in 16-byte pieces
+// all the same.
+typedef float four __attribute__((ext_vector_type(4), aligned(4)));
 __global__ __launch_bounds__(256) void k_bce(const float* __restrict__ Z, const uint32_t* __restrict__ lab,
                                              const uint32_t* __restrict__ valid, int batch, int nout,
                                              float* __restrict__ G, int64_t ldg, double* __restrict__ denom,
@@ -701,9 +704,8 @@ __global__ __launch_bounds__(256) void k_bce(const float* __restrict__ Z, const 
     const int64_t b = q / per_row;
     const int o = (int)(q - b * per_row) * kBcePiece + 4 * threadIdx.x;
     if (o >= nout) continue;   // nout is a multiple of 32: four outputs share a word
-    const float4 z4 = *reinterpret_cast<const float4*>(Z + b * nout + o);
+    const f32x4 zz = *reinterpret_cast<const four*>(Z + b * nout + o);
     const uint32_t okw = valid[o >> 5] >> (o & 31), yw = lab[b * words + (o >> 5)] >> (o & 31);
-    const float zz[4] = {z4.x, z4.y, z4.z, z4.w};
     float g[4];
 #pragma unroll
     for (int j = 0; j < 4; ++j) {

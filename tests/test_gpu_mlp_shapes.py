@@ -104,3 +104,20 @@ def test_every_kernel_gives_a_row_the_same_bits():
     for b in (1, 16, 17, 32, 33, 64, 65, 128):
         say(f"case: batch {b} of 200")
         assert torch.equal(mlp.forward(x[:b]), full[:b])
+
+
+@pytest.mark.parametrize("offset", [1, 2, 3])
+def test_logits_need_no_alignment_but_their_elements(offset):
+    """The loss reads the caller's logits wherever they lie: the same bits."""
+    say(f"case: logits {4 * offset} bytes past a 16-byte boundary")
+    mlp = P.MLP([16, 64, 1056], seed=95)
+    g = torch.Generator(device="cuda").manual_seed(96)
+    x = torch.randn((37, 16), generator=g, device="cuda")
+    lab = torch.randint(0, 1 << 31, (37, 33), generator=g, device="cuda", dtype=torch.int64).to(torch.int32)
+    valid = torch.full((33,), -1, dtype=torch.int32, device="cuda")
+    z = mlp.forward(x)
+    want = mlp.backward(x, z, lab, valid).clone(), mlp.grad.clone()
+    buf = torch.empty(z.numel() + 4, device="cuda")
+    far = buf[offset:offset + z.numel()].view(z.shape)
+    assert torch.equal(mlp.forward(x, far), z) and far.data_ptr() % 16 == 4 * offset
+    assert torch.equal(mlp.backward(x, far, lab, valid), want[0]) and torch.equal(mlp.grad, want[1])
