@@ -35,8 +35,9 @@ __device__ inline uint16_t bf16_bits(float f) {
   return (uint16_t)(u >> 16);
 }
 
-// The same rounding of two values at once (v_cvt_pk_bf16_f32: equal to
-// bf16_bits on every finite pattern and infinity, a NaN stays a NaN).
+// The same rounding of two values at once (v_cvt_pk_bf16_f32: the tests compare
+// it with bf16_bits where both halves of a value are normal numbers; a NaN stays
+// a NaN).
 __device__ __forceinline__ uint32_t bf16_pair(float a, float b) {
   const f32x2 v = {a, b};
   return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2));

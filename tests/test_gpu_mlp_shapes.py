@@ -121,3 +121,103 @@ def test_logits_need_no_alignment_but_their_elements(offset):
     far = buf[offset:offset + z.numel()].view(z.shape)
     assert torch.equal(mlp.forward(x, far), z) and far.data_ptr() % 16 == 4 * offset
     assert torch.equal(mlp.backward(x, far, lab, valid), want[0]) and torch.equal(mlp.grad, want[1])
+
+
+def one_layer(n_in, n_out, hidden=None):
+    return P.MLP([n_in, n_out] if hidden is None else [n_in, hidden, n_out], seed=97)
+
+
+def test_forward_tiles_give_the_same_bits():
+    """64 x 64 tiles (65 rows, 8192 wide), 128 x 128 (1100 rows) and the direct kernel
+    (1, 17, 64 rows)."""
+    mlp = one_layer(264, 8192)
+    x = torch.randn((1100, 264), generator=torch.Generator(device="cuda").manual_seed(98), device="cuda")
+    full = mlp.forward(x).clone()
+    for b in (1, 17, 64, 65, 200):
+        say(f"case: {b} of 1100 rows")
+        assert torch.equal(mlp.forward(x[:b]), full[:b])
+
+
+def test_input_gradient_kernels_give_the_same_bits():
+    """The chain kernel (256 rows) and 128 x 128 tiles (16384 rows): the first
+    layer's weight gradient where one row counts is that row's input gradient times
+    its input.  The other rows' inputs, and so their hidden units, are zero; rows
+    and counted outputs are powers of two, so that dL/dz differs by a factor that
+    is one."""
+    mlp = one_layer(8, 2080, hidden=512)
+    g = torch.Generator(device="cuda").manual_seed(99)
+    row = torch.randn(8, generator=g, device="cuda")
+    bits = torch.randint(0, 1 << 31, (65,), generator=g, device="cuda", dtype=torch.int64).to(torch.int32)
+    valid = torch.full((65,), -1, dtype=torch.int32, device="cuda")
+    valid[64] = 0
+    got = []
+    for rows in (256, 16384):
+        say(f"case: {rows} rows")
+        x = torch.zeros((rows, 8), device="cuda")
+        x[3] = row
+        lab = torch.zeros((rows, 65), dtype=torch.int32, device="cuda")
+        lab[3] = bits
+        mlp.backward(x, mlp.forward(x), lab, valid)
+        got.append(mlp.split(mlp.grad)[0][0] * rows)
+    assert got[0].any() and torch.equal(*got)
+
+
+@pytest.mark.parametrize("n_out,n_in", [(8192, 512), (2176, 520), (32768, 256)])
+def test_weight_gradient_tiles_give_the_same_bits(n_out, n_in):
+    """The first rows and columns of a large weight gradient (64 x 64 or 128 x 128
+    tiles) and the small one of those alone (32 x 32 tiles): 32 outputs and 64
+    inputs of the layer, over 256 rows.  Their logits are the same, as the other
+    inputs' weights are zero, and the other outputs do not count."""
+    say(f"case: {n_out} x {n_in}")
+    g = torch.Generator(device="cuda").manual_seed(102)
+    x = torch.randn((256, n_in), generator=g, device="cuda")
+    w = torch.randn((32, 64), generator=g, device="cuda") / 8
+    lab = torch.randint(0, 1 << 31, (256, 1), generator=g, device="cuda", dtype=torch.int64).to(torch.int32)
+    got = []
+    for o, i in ((32, 64), (n_out, n_in)):
+        mlp = one_layer(i, o)
+        W = torch.zeros((o, i), device="cuda")
+        W[:32, :64] = w
+        mlp.set_weights([W.cpu().numpy()], [torch.zeros(o).numpy()])
+        xs = x[:, :i].contiguous()
+        z = mlp.forward(xs)
+        valid = torch.zeros(o // 32, dtype=torch.int32, device="cuda")
+        valid[0] = -1
+        labs = torch.zeros((256, o // 32), dtype=torch.int32, device="cuda")
+        labs[:, :1] = lab
+        mlp.backward(xs, z, labs, valid)
+        dw, db = mlp.split(mlp.grad)[0]
+        got.append((dw[:32, :64].clone(), db[:32].clone()))
+    assert got[0][0].any() and torch.equal(got[0][0], got[1][0]) and torch.equal(got[0][1], got[1][1])
+
+
+def test_the_halves_of_a_float():
+    """An FP32 operand enters the products as bf16 halves hi + lo, rounded by the
+    hardware: the same as rounding to nearest even by integers, for ties, both
+    sides of them, and every exponent at which the low half is a normal number."""
+    rng = np.random.Generator(np.random.PCG64(103))
+    exps = np.arange(26, 254, dtype=np.uint32)
+    low = np.concatenate([np.arange(0x7F00, 0x8100), [0, 1, 2, 0xFFFF, 0xFFFE], rng.integers(0, 1 << 16, 800)]).astype(np.uint32)
+    top = rng.integers(0, 128, (exps.size, low.size)).astype(np.uint32)
+    sign = rng.integers(0, 2, top.shape).astype(np.uint32) << 31
+    f = (sign | exps[:, None] << 23 | top << 16 | low[None, :]).reshape(-1)
+    f = f[: f.size // 8 * 8].view(np.float32)
+
+    def nearest(v):
+        u = v.view(np.uint32).astype(np.uint64)
+        return ((u + 0x7FFF + (u >> 16 & 1)) & 0xFFFF0000).astype(np.uint32).view(np.float32)
+
+    hi = nearest(f)
+    fits = np.isfinite(hi)
+    f, hi = f[fits], hi[fits]
+    f, hi = f[: f.size // 8 * 8], hi[: f.size // 8 * 8]
+    lo = nearest(f - hi)
+    W = np.zeros((32, 8), np.float32)
+    W[:8, :8] = np.eye(8)
+    mlp = one_layer(8, 32)
+    mlp.set_weights([W], [np.zeros(32, np.float32)])
+    x = torch.tensor(f.reshape(-1, 8), device="cuda")
+    say(f"case: {f.size} values")
+    for rows in (x[:64], x):
+        z = mlp.forward(rows)[:, :8].cpu().numpy()
+        assert np.array_equal(z.reshape(-1), (hi + lo)[: z.size])
