@@ -72,8 +72,8 @@ struct OffsetsMarkOut {
   uint32_t n_mark;
   __device__ void marks(int64_t i, uint32_t off, uint32_t v) const {
     const uint64_t end = (uint64_t)off + v;
-    for (uint64_t b = ((uint64_t)off + ((1u << kMarkShift) - 1)) >> kMarkShift; (b << kMarkShift) < end && b < n_mark; ++b)
-      mark[b] = (uint32_t)i;
+    uint64_t b = ((uint64_t)off + ((1u << kMarkShift) - 1)) >> kMarkShift;
+    for (; (b << kMarkShift) < end && b < n_mark; ++b) mark[b] = (uint32_t)i;
   }
   __device__ void operator()(int64_t i, uint32_t off, uint32_t v) const {
     out[i] = off;
@@ -396,7 +396,8 @@ __device__ __forceinline__ void tile_rank(const uint32_t* __restrict__ keys, con
     uint32_t plo = (uint32_t)on, phi = (uint32_t)(on >> 32);
 #pragma unroll
     for (int b = 0; b < 8; ++b) {
-      const uint32_t x = (uint32_t)__builtin_amdgcn_sbfe((int)key[r], (uint32_t)(shift + b), 1u);   // the bit, in all places
+      // the bit, in all places
+      const uint32_t x = (uint32_t)__builtin_amdgcn_sbfe((int)key[r], (uint32_t)(shift + b), 1u);
       const uint64_t mk = __ballot(x != 0u);
       plo = __builtin_amdgcn_bitop3_b32(plo, (uint32_t)mk, x, 0x90);   // a & ~(b ^ c)
       phi = __builtin_amdgcn_bitop3_b32(phi, (uint32_t)(mk >> 32), x, 0x90);
@@ -520,7 +521,7 @@ void radix_sort_pairs(uint32_t* ka, uint32_t* va, uint32_t* kb, uint32_t* vb, in
 // The same stable LSD sort with one kernel per 8-bit pass.  A first kernel
 // counts every pass's digits over all keys at once (LDS bins per block,
 // added to global counts with device-scope atomics).  Each pass kernel then
-// ranks its 4096-key tile as k_radix_scatter does, publishes its digit
+// ranks its tile of 64 W R keys as k_radix_scatter does, publishes its digit
 // counts, and finds the counts of all earlier tiles by walking back over
 // their published words until one holds an inclusive prefix (decoupled
 // look-back, kOsWindow words per poll).  A tile publishes its own counts

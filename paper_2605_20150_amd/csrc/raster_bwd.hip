@@ -34,16 +34,17 @@ __device__ __forceinline__ void entry_factors(T op, T A, T B, T C, Rec9<T>& r) {
 }
 
 // ----------------------------------------------------- compositing adjoint
-// Same lane/pixel layout as the forward.  Each pixel walks back from its
-// last contributor, recovering T_i = T_{i+1} / (1 - alpha_i) and the
+// One wave per tile, four pixels per lane: lane l holds column l % 16 and rows
+// l / 16, + 4, + 8 and + 12.  Each pixel walks back from its last contributor, recovering T_i = T_{i+1} / (1 - alpha_i) and the
 // normalised colour behind the entry (r_{i-1} = alpha_i c_i + (1-alpha_i) r_i,
 // starting from the background).  The per-pixel update is branch-free; the
 // four pixels of a lane are summed in registers, each row of 16 lanes is
 // reduced with DPP and the four row sums are parked in LDS; once a batch of
 // 32 entries is done, lane k adds entry k's four row sums, applies the
-// entry's factors (opacity, conic) and stores its partial.  (Batches of 32 keep the parked sums at the LDS size that 64
-// entries with rows added in pairs took, so occupancy is unchanged, and each
-// taken entry saves the nine pair additions.)  An entry some pixel takes is
+// entry's factors (opacity, conic) and stores its partial.  (Batches of 32 keep
+// the parked sums at the LDS size that 64 entries with rows added in pairs took,
+// so occupancy is unchanged, and each taken entry saves the nine pair
+// additions.)  An entry some pixel takes is
 // marked in `taken` (one byte per emission index, zero on entry unless mark_all,
 // which has the kernel write every byte); the others get no partial, and the
 // per-pair sums pass over them.  At street level most entries lie behind the
@@ -283,7 +284,6 @@ __global__ void __launch_bounds__(64) k_render_bwd(const uint32_t* __restrict__ 
 // wave per tile, which does less per entry, to be the faster one: 5800 tiles
 // (out-of-core walk, 4 x 800x450) 93 against 130 us here, 8160 (1M aerial,
 // 1920x1080) 600 against 900.
-template <typename T>
 constexpr int kBwdBatch = 12;
 template <typename T>
 constexpr int kBwdLong = sizeof(T) == 4 ? 24 : 12;
@@ -929,8 +929,9 @@ struct AdamRows {
 
 template <typename T, bool kAdam>
 __device__ __forceinline__ void adjoint_row(T* params, const int32_t* __restrict__ order, int32_t B, int64_t n_pidx,
-                                            const CamSet<T>& cs, const uint32_t* __restrict__ tt, const uint8_t* __restrict__ g2d_on,
-                                            const uint32_t* __restrict__ active, const uint32_t* __restrict__ act_idx,
+                                            const CamSet<T>& cs, const uint32_t* __restrict__ tt,
+                                            const uint8_t* __restrict__ g2d_on, const uint32_t* __restrict__ active,
+                                            const uint32_t* __restrict__ act_idx,
                                             const T* __restrict__ g2d, T* __restrict__ grad, int64_t ld,
                                             const AdamRows<T>& ad) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -942,7 +943,10 @@ __device__ __forceinline__ void adjoint_row(T* params, const int32_t* __restrict
   const int V = cs.n;
   uint32_t keepm = 0;
 #pragma unroll 1
-  for (int c = 0; c < V; ++c) keepm |= ((!tt || tt[(int64_t)c * n_pidx + i] != 0) && g2d_on[(int64_t)c * n_pidx + i] != 0 ? 1u : 0u) << c;
+  for (int c = 0; c < V; ++c) {
+    const int64_t o = (int64_t)c * n_pidx + i;
+    keepm |= ((!tt || tt[o] != 0) && g2d_on[o] != 0 ? 1u : 0u) << c;
+  }
   T bcx = 0, bcy = 0;
   if constexpr (kAdam) adam_step_bias<T>(ad.step + (int64_t)slot * B + row, ad.lb1, ad.lb2, bcx, bcy);
   // Adam state (m, v) of column j; a group of columns loads its states
@@ -1078,7 +1082,8 @@ __device__ __forceinline__ void adjoint_row(T* params, const int32_t* __restrict
 
 template <typename T>
 __global__ void __launch_bounds__(256) k_adjoint(T* params, const int32_t* __restrict__ order, int32_t B,
-                                                 int64_t n_pidx, CamSet<T> cs, const uint32_t* __restrict__ tt, const uint8_t* __restrict__ g2d_on,
+                                                 int64_t n_pidx, CamSet<T> cs, const uint32_t* __restrict__ tt,
+                                                 const uint8_t* __restrict__ g2d_on,
                                                  const uint32_t* __restrict__ active,
                                                  const uint32_t* __restrict__ act_idx, const T* __restrict__ g2d,
                                                  T* __restrict__ grad, int64_t ld) {
@@ -1090,7 +1095,8 @@ __global__ void __launch_bounds__(256) k_adjoint(T* params, const int32_t* __res
 template <typename T>
 __global__ void __launch_bounds__(256, 4) k_adjoint_adam(T* params, const int32_t* __restrict__ order, int32_t B,
                                                          int64_t n_pidx, CamSet<T> cs,
-                                                         const uint32_t* __restrict__ tt, const uint8_t* __restrict__ g2d_on,
+                                                         const uint32_t* __restrict__ tt,
+                                                         const uint8_t* __restrict__ g2d_on,
                                                          const uint32_t* __restrict__ active,
                                                          const uint32_t* __restrict__ act_idx,
                                                          const T* __restrict__ g2d, AdamRows<T> ad) {
@@ -1099,8 +1105,7 @@ __global__ void __launch_bounds__(256, 4) k_adjoint_adam(T* params, const int32_
 
 template <typename T>
 static void launch_adjoint(const tide_pool* pool, const tide_proj* proj, const CamSet<T>& cs, const uint32_t* tt,
-                           const uint8_t* g2d_on, const T* g2d,
-                           T* grad, int64_t ld, hipStream_t st) {
+                           const uint8_t* g2d_on, const T* g2d, T* grad, int64_t ld, hipStream_t st) {
   hipLaunchKernelGGL(k_adjoint<T>, dim3((uint32_t)ceil_div(proj->n_pidx, 256)), dim3(256), 0, st,
                      (T*)pool->params, pool->order, pool->block_rows, proj->n_pidx, cs, tt, g2d_on,
                      proj->active, proj->act_idx, g2d, grad, ld);
@@ -1108,8 +1113,7 @@ static void launch_adjoint(const tide_pool* pool, const tide_proj* proj, const C
 
 template <typename T>
 static void launch_adjoint_adam(const tide_pool* pool, const tide_proj* proj, const CamSet<T>& cs, const uint32_t* tt,
-                           const uint8_t* g2d_on, const T* g2d,
-                                const tide_adam_cfg* cfg, hipStream_t st) {
+                                const uint8_t* g2d_on, const T* g2d, const tide_adam_cfg* cfg, hipStream_t st) {
   AdamRows<T> ad;
   ad.m1 = (T*)pool->exp_avg;
   ad.m2 = (T*)pool->exp_avg_sq;
@@ -1201,11 +1205,11 @@ static tide_status render_bwd_t(const tide_pool* pool, const tide_camera* cams, 
                          bins->inst_rec, (const T*)proj->rec, bins->tiles_x, bins->tiles_y, fr->width, fr->height,
                          (T)bg[0], (T)bg[1], (T)bg[2], (const T*)fr->t_final, fr->last, (const T*)d_dimage, w.partial,
                          w.taken, mark_all);
-    } else if (grid <= kLongTiles || kBwdLong<T> == kBwdBatch<T>) {
+    } else if (grid <= kLongTiles || kBwdLong<T> == kBwdBatch) {
       split(k_render_bwd_split<T, kBwdLong<T>>, kAllTiles);   // nothing shares a CU
     } else {
       split(k_render_bwd_split<T, kBwdLong<T>>, kIfLong);
-      split(k_render_bwd_split<T, kBwdBatch<T>>, kIfEven);
+      split(k_render_bwd_split<T, kBwdBatch>, kIfEven);
     }
   };
   TIDE_TIMED("render_bwd", st, render());

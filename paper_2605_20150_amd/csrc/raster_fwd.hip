@@ -70,11 +70,12 @@ template CamSet<double> make_camset<double>(const tide_camera*, int);
 // share the time: street level, 20M Gaussians, 4 cameras (30 % of the pairs in
 // view) 1145 us without the bound and 919 us with it; aerial, 1M, 4 cameras 79
 // and 73 us.  Columns of a block are contiguous, so lanes (consecutive rows)
-// read coalesced.  The camera-space position and the pixel position are computed in double: at aerial scales (|p| ~ 300 m,
-// f ~ 1700 px) single precision would put ~3e-4 px of error on u, v, which a
-// sub-pixel footprint turns into flipped alpha >= 1/255 decisions; rounding
-// the double result once leaves at most half an ulp of u.  This costs a few
-// FP64 operations per (Gaussian, camera) in a bandwidth-bound kernel.
+// read coalesced.  The camera-space position and the pixel position are computed
+// in double: at aerial scales (|p| ~ 300 m, f ~ 1700 px) single precision would
+// put ~3e-4 px of error on u, v, which a sub-pixel footprint turns into flipped
+// alpha >= 1/255 decisions; rounding the double result once leaves at most half
+// an ulp of u.  This costs a few FP64 operations per (Gaussian, camera) in a
+// bandwidth-bound kernel.
 __device__ inline double cam_depth(const double* Rd, const double* td, double m0, double m1, double m2) {
   return Rd[6] * m0 + Rd[7] * m1 + Rd[8] * m2 + td[2];
 }
@@ -87,11 +88,13 @@ __device__ inline double cam_depth(const double* Rd, const double* td, double m0
 // rounding of both sides.  Everything is multiplied by the depth: no division.
 // NaN and infinite bounds pass.
 template <typename T>
-__device__ __forceinline__ bool may_meet_image(const DevCam<T>& cm, double m0, double m1, double m2, double pz, T smax) {
+__device__ __forceinline__ bool may_meet_image(const DevCam<T>& cm, double m0, double m1, double m2, double pz,
+                                               T smax) {
   const double x = cm.fxd * (cm.Rd[0] * m0 + cm.Rd[1] * m1 + cm.Rd[2] * m2 + cm.td[0]) + cm.cxd * pz;
   const double y = cm.fyd * (cm.Rd[3] * m0 + cm.Rd[4] * m1 + cm.Rd[5] * m2 + cm.td[1]) + cm.cyd * pz;
   const double r = cm.reach * (double)smax + 18.7 * pz;   // 17 + 3.03 sqrt 0.3
-  const bool out = x + r < 0 || y + r < 0 || x - r > (double)(kTile * cm.Tx) * pz || y - r > (double)(kTile * cm.Ty) * pz;
+  const bool out = x + r < 0 || y + r < 0 || x - r > (double)(kTile * cm.Tx) * pz ||
+                   y - r > (double)(kTile * cm.Ty) * pz;
   return !(out && pz > 0);
 }
 
@@ -423,9 +426,9 @@ struct PairRectOut {
 // by pairs: the nearest pairs come first and cover thousands of tiles each at
 // street level, and a wave that took 64 of them ran long after the rest
 // (20M Gaussians, 4 x 1600x900: 2705 us by pairs, 400 us now; 1M from above,
-// where footprints are even: 37 and 39 us).  Instances at or past cap are not written (the call then reports the count it
-// needs).  The grid also clears zero[0, n_zero) (the tile ranges, filled in
-// later).
+// where footprints are even: 37 and 39 us).  Instances at or past cap are not
+// written (the call then reports the count it needs).  The grid also clears
+// zero[0, n_zero) (the tile ranges, filled in later).
 constexpr int kEmitWaves = 32768;       // pieces aimed at: four times what the chip holds at once
 constexpr int64_t kEmitMin = 1 << kMarkShift, kEmitMax = 2048;
 __global__ void __launch_bounds__(64) k_emit(const uint32_t* __restrict__ first, const uint32_t* __restrict__ width,
@@ -671,8 +674,8 @@ __global__ void __launch_bounds__(kOrderTiles) k_order_place(const uint32_t* __r
 }
 
 // The depth sort's tiles: kDepthWaves waves of kDepthRounds keys per lane.
-// 4096-key tiles were faster than 2048 or 1024 (fewer look-back words to
-// publish and read), and eight waves of eight rounds faster than four of
+// With a million pairs and more, 4096-key tiles were faster than 2048 or 1024
+// (fewer look-back words to publish and read), and eight waves of eight rounds faster than four of
 // sixteen (124 against 144 us for the four passes over 2.25 M keys: a
 // tile's ranking is a chain of rounds), sixteen of four no faster.
 constexpr int kDepthWaves = 8;
@@ -769,10 +772,10 @@ static BinLayout bin_layout(void* ws, int n_cams, int64_t n_pidx, int64_t n_tile
 // Before (one wave per tile) and now: 4 x 1920x1080, 1M Gaussians 605 and 526
 // us; 1237x823, 300k 650 and 167 us; 64x64 83 and 21 us.  Footprints that cover
 // whole tiles gain nothing from quadrants: street level, 20M, 320 and 394 us of
-// an 18 ms step.  One entry at a time 566 us (aerial), two 535, four 548;
+// an 8.5 ms step.  One entry at a time 566 us (aerial), two 535, four 548;
 // batches of 128 the same.  One wave per tile that skips quadrants by branches:
 // 1012 us.
-constexpr int kFwdBatch = 64, kFwdGroup = 3;
+constexpr int kFwdBatch = kWave, kFwdGroup = 3;   // an entry per lane of the footprint test
 constexpr int kFwdSlots = kFwdBatch + kWave;   // the arrays keep a multiple of 64 apart: pairs of reads fuse
 
 template <typename T>
@@ -807,7 +810,8 @@ __global__ void __launch_bounds__(256) k_render_fwd(const uint32_t* __restrict__
   // entry fields; slot kFwdBatch is one that no pixel takes (opacity 0), which
   // fills up the last group of a walk
   __shared__ T s_u[kFwdSlots], s_v[kFwdSlots], s_A[kFwdSlots], s_B[kFwdSlots], s_C[kFwdSlots],
-      s_o[kFwdSlots], s_r[kFwdSlots], s_g[kFwdSlots], s_b[kFwdSlots], s_ka[kFwdBatch], s_kc[kFwdBatch], s_lim[kFwdBatch];
+      s_o[kFwdSlots], s_r[kFwdSlots], s_g[kFwdSlots], s_b[kFwdSlots], s_ka[kFwdBatch], s_kc[kFwdBatch],
+      s_lim[kFwdBatch];
   __shared__ uint32_t s_live[4];
   const T ks = (T)Ex<T>::k;
   const int tid = threadIdx.x;
@@ -842,21 +846,19 @@ __global__ void __launch_bounds__(256) k_render_fwd(const uint32_t* __restrict__
       if (left > (uint32_t)(kFwdBatch + tid)) load(r_n);
       if (left > (uint32_t)(2 * kFwdBatch + tid)) r_n = inst_rec[inst_e[b0 + 2 * kFwdBatch + tid]];
     }
-#pragma unroll
-    for (int h = 0; h < kFwdBatch; h += kWave) {
-      if (nlive == 0 || left <= (uint32_t)h) break;
-      const int k0 = h + lane;
+    if (nlive != 0) {
       bool may = false;
       // entries whose footprint misses every pixel centre of the quadrant at
       // alpha >= 1/255 are passed over without any per-pixel work
-      if (left > (uint32_t)k0)
-        may = box_may_take<kQ, kQ, T>(s_u[k0], s_v[k0], s_A[k0], s_B[k0], s_C[k0], s_ka[k0], s_kc[k0], s_lim[k0], qx, qy);
+      if (left > (uint32_t)lane)
+        may = box_may_take<kQ, kQ, T>(s_u[lane], s_v[lane], s_A[lane], s_B[lane], s_C[lane], s_ka[lane], s_kc[lane],
+                                      s_lim[lane], qx, qy);
       uint64_t rest = __ballot(may);
       while (rest != 0) {
         int k[kFwdGroup];
 #pragma unroll
         for (int i = 0; i < kFwdGroup; ++i) {
-          k[i] = rest != 0 ? h + (int)__builtin_ctzll(rest) : kFwdBatch;
+          k[i] = rest != 0 ? (int)__builtin_ctzll(rest) : kFwdBatch;
           rest &= rest - 1;   // 0 stays 0
         }
         // Alphas first: when no pixel takes an entry (the quadrant test is
@@ -1142,8 +1144,9 @@ extern "C" tide_status tide_bin_sort(const tide_proj* proj, int32_t tiles_x, int
   {
     const int64_t pieces = ceil_div(cap > 0 ? cap : 1, kEmitMin);
     TIDE_TIMED("emit", st, hipLaunchKernelGGL(k_emit, dim3((uint32_t)(pieces < kEmitWaves ? pieces : kEmitWaves)),
-                                              dim3(kWave), 0, st, pfirst, L.pwidth, vrec, L.inst_off, L.mark, nv, &L.totals[0],
-                                              cap, &L.totals[2], tiles_x, L.tka, L.inst_rec, L.ranges, nr));
+                                              dim3(kWave), 0, st, pfirst, L.pwidth, vrec, L.inst_off, L.mark, nv,
+                                              &L.totals[0], cap, &L.totals[2], tiles_x, L.tka, L.inst_rec, L.ranges,
+                                              nr));
   }
   TIDE_LAUNCH_CHECK("k_emit");
   // 6. stable sort by tile; values are emission indices (histogram, scan
