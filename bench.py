@@ -46,13 +46,16 @@ HBM_BOUND = ("preprocess", "reduce_pairs", "adjoint", "adam", "adjoint_adam", "l
 # hash of the kernel's sources when they were taken: the figure is reported
 # only while the sources are unchanged.
 TRAFFIC = {"render_bwd": {"bytes": 3499.3e6, "sources": ["raster_bwd.hip", "raster.h"],
-                          "sha256_16": "6a7dbbb9c19882df"}}
+                          "sha256_16": "5b571e7f6998b6fe"}}
 # Executed-instruction view of the dominant kernel from one SQ counter pass
 # of this benchmark (profiles/render_aerial1M_sq_instructions.md): VALU
 # wave-instructions per launch and the busy cycles per VALU instruction of a
-# SIMD (4 cycles is one wave64 instruction back to back on a 16-lane SIMD),
-# reported while the kernel's sources are those the counters were taken on.
-ISSUE = {"render_bwd": {"valu_wave_instr": 681.2e6, "cycles_per_valu_per_simd": 3.48,
+# SIMD, reported while the kernel's sources are those the counters were taken
+# on.  What an instruction takes with many waves in flight: 2.3 cycles for an
+# FP32 addition, multiplication or FMA whose operands are vector registers or
+# constants, 4.1 with a scalar register, and for DPP, comparisons, selects,
+# minima, maxima and conversions, 8.1 for an exponential or a reciprocal.
+ISSUE = {"render_bwd": {"valu_wave_instr": 685.0e6, "cycles_per_valu_per_simd": 3.48,
                         "sources": ["raster_bwd.hip", "raster.h"], "sha256_16": TRAFFIC["render_bwd"]["sha256_16"]}}
 # The step runs the backward's last stage and the masked Adam update as one
 # kernel (adjoint_adam); adjoint and adam are the same two stages as separate
@@ -147,8 +150,8 @@ def measured_issue(kernel):
         return None
     return {"valu_wave_instr_per_launch": t["valu_wave_instr"],
             "cycles_per_valu_per_simd": t["cycles_per_valu_per_simd"],
-            "note": "rocprofv3 SQ_INSTS_VALU and GRBM_GUI_ACTIVE / 8 over 1024 SIMDs; 4 cycles per wave64 "
-                    "VALU instruction is back-to-back issue"}
+            "note": "rocprofv3 SQ_INSTS_VALU and GRBM_GUI_ACTIVE / 8 over 1024 SIMDs; back to back this kernel's "
+                    "mix of VALU instructions takes about 3.2 cycles each"}
 
 
 def _oracle_iteration(oracle, th, cm, targets):

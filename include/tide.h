@@ -17,12 +17,13 @@
  *     must be device (HBM) pointers; "host" pointers are ordinary memory.
  *     The library never allocates device memory on the per-iteration path;
  *     calls that need scratch take a caller workspace (ws, ws_bytes) and
- *     report the size they need.  Device buffers and workspaces must be at
- *     least 8-byte aligned (f64 data: 8; records of four-byte values are
- *     moved as unaligned 16-byte pieces, which need 4); 256-byte alignment,
- *     what hipMalloc and torch give, lets the scans, histograms and range
- *     pass of tide_bin_sort use 16-byte accesses (they fall back to
- *     one-element accesses otherwise).
+ *     report the size they need; sizes grow with the problem, so a workspace
+ *     for the largest one serves every smaller one.  Device buffers and
+ *     workspaces must be at least 8-byte aligned (f64 data: 8; records of
+ *     four-byte values are moved as unaligned 16-byte pieces, which need 4);
+ *     256-byte alignment, what hipMalloc and torch give, lets the scans,
+ *     histograms and range pass of tide_bin_sort use 16-byte accesses (they
+ *     fall back to one-element accesses otherwise).
  *   - Device work is enqueued on the HIP stream passed as `stream`
  *     (a hipStream_t; NULL = the default stream) and is asynchronous unless a
  *     call says it blocks.
@@ -66,6 +67,8 @@ int32_t tide_abi_version(void);
  * Cameras (host structs).  World-to-camera p_cam = R p_world + t, R
  * row-major, OpenCV axes (x right, y down, z forward).  Pixel (i, j) is
  * sampled at (i + 0.5, j + 0.5).  Tiles are 16 x 16, ceil(W/16) x ceil(H/16).
+ * The rasterizer projects with any R; the colour's viewing direction (camera
+ * centre -R^T t) and the block frustum test take it for a rotation.
  * z_near / z_far cull a Gaussian whose camera depth is <= z_near or > z_far;
  * the same planes bound the block frustum test of tide_cull_blocks.
  * ---------------------------------------------------------------------- */

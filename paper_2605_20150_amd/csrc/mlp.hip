@@ -191,9 +191,10 @@ __global__ __launch_bounds__(256) void k_gemm_direct(const float* __restrict__ A
 // accumulators per lane and reads each operand half as often as T = 64; T = 32
 // is for the products too small to fill the chip, where the staging of a
 // workgroup is what it waits for.
-// 256 x 512 -> 65536: forward 65 us (115 us with 64 x 64 tiles, integer
-// rounding and no loads in flight), weight gradient 88 us (335 us, of which
-// 62 us the bias gradient as a kernel of its own; 149 us with checked loads).
+// 256 x 512 -> 65536: forward 65 us in a training step and 57 us in scoring (115
+// us with 64 x 64 tiles, integer rounding and no loads in flight), weight
+// gradient 88 us (335 us, of which 62 us the bias gradient as a kernel of its
+// own; 149 us with checked loads).
 // Weight gradient 256 x 512 -> 512: 7.4 us (18.7 us with 64 x 64 tiles and
 // checked loads, 11.8 us with the tiles alone).
 //
@@ -431,7 +432,7 @@ __global__ __launch_bounds__(256) void k_gemm(const float* __restrict__ A, int64
 // else, eight more hold two stages of 256 k in flight in registers, round G
 // into its halves and transpose W on the way into LDS.  The tile is 16 x 64
 // because 64 columns are whole 128-byte lines of W's rows (16 x 32 on twice
-// the CUs measured 285 us).  Batch 256, 65536 -> 512: 230 us (64 x 64 tiles on
+// the CUs measured 285 us).  Batch 256, 65536 -> 512: 215 us (64 x 64 tiles on
 // 32 workgroups with a barrier per 32 k: 3980 us); its loads alone take 195 us,
 // its staging alone 118 us, its products alone 142 us.
 // Grid: super-tiles of 4 x 4 workgroups, one per XCD, that share G rows and W
@@ -605,7 +606,7 @@ void launch_direct(hipStream_t st, const float* A, int64_t lda, const uint16_t* 
 // One forward layer.  Up to 64 rows, and wherever 64 x 64 tiles would give
 // fewer than one workgroup per CU, the direct kernel is the faster one (at 256
 // x 512 x 512 7.6 us against 32 us); from 512 workgroups on the larger tile is
-// (256 x 512 x 65536 66 us against 73 us).  The direct kernel takes several
+// (256 x 512 x 65536 65 us against 73 us).  The direct kernel takes several
 // row tiles per wave once that leaves two waves per SIMD, so that the weights
 // are read once.
 template <int EPI>
@@ -672,12 +673,12 @@ constexpr int kLossBlocks = 1024;
 // G = (sigmoid(z) - y) / denom on valid outputs (0 elsewhere), rows of ldg
 // floats; per-block partial sums of the element losses in double, fixed
 // order.  denom = batch * (number of valid outputs), which every block counts
-// for itself (8 KB of words at most in L2, one launch fewer); block 0 leaves
+// for itself (8 KB of words for 65536 outputs, from L2: one launch fewer); block 0 leaves
 // it for k_loss_sum.  A thread takes four neighbouring outputs of a
 // 1024-output piece of a row with one 16-byte load and store; blocks take
 // pieces grid-stride.  Reads and writes 4 B per output each; the exponential,
 // the logarithm and the double-precision sum bound it: 256 x 65536 (134 MB)
-// 72 us, 86 us with one output per thread and an index division each.
+// 66 us, 86 us with one output per thread and an index division each.
 constexpr int kBcePiece = 1024;
 // The logits are the caller's, aligned to their element: moved in 16-byte pieces
 // all the same.

@@ -193,7 +193,9 @@ __device__ __forceinline__ double alpha_clamped(double araw, bool below) {
 // edge's least Q by 4 and by 8 for the box's rounded sides; 32 u S are allowed.
 // The terms of a long oblique footprint cancel, so S is far above Q there (a
 // footprint of 3000 px: without S, 20 of 350 000 taken pixels were passed over by
-// one 8 x 8 box or another); for a round one S is Q or so, and nothing changes.
+// one 8 x 8 box or another); for a round one S is Q or so, and the boxes stay the
+// same.  1M Gaussians, 4 x 1920x1080: 2.5 % more vector instructions in the forward
+// and 0.5 % in the backward, 524 and 990 to 995 us as before.
 // A slack of 1e-3 (relative and absolute) covers the exponential and the logarithm.
 // box_prepare forms what does not depend on the box, once per entry: the slopes
 // of the stationary points, -B/A and -B/C, and the bound on Q/2 in the scaled
